@@ -6,29 +6,35 @@
 // Two passes over K, both with the query-window x key contraction on the bf16 MFMA
 // (v_mfma_f32_32x32x16_bf16, fp32 accumulate), because a softmax row must be normalized before it
 // can be summed into a column:
-//   pass A  row statistics: running max and sum of exponentials per window row, per key chunk;
+//   pass A  row statistics: a reference exponent and the sum of exponentials per window row, per key chunk;
 //   combine per-row bias b_r = max_r + log2(sum_r) over all chunks (a tiny kernel, or the prologue of pass B
 //           when there are few chunks);
 //   pass B  column sums: scores[t] = sum_r 2^(s_rt - b_r).
 // Logits are kept in the base-2 domain (s = q.k * log2(e)/sqrt(D)) so the exponential is one
 // v_exp_f32.
 //
-// Tiling.  A block is 8 waves and owns one key chunk of one (layer, kv head).  The window queries
-// (at most 512 rows) are staged once per block in LDS (row pitch 272 B so that the 16-byte operand
-// reads of 8 lanes cover all 32 banks).  Every wave then works alone, without block barriers: it
-// owns every 8th 32-key tile of the chunk, loads a tile straight from global memory into MFMA operand registers
-// (the next tile is fetched while the current one is consumed), and walks all query tiles against
-// it in a software pipeline (the MFMAs of query tile n+1 are issued before the vector-ALU work of
-// tile n).  The MFMA operand layout is the same for A and B (lane = row or column index mod 32,
-// 8 consecutive channels per lane, lanes 32..63 take the upper 8 of each 16-channel step), so the
-// same registers serve both orientations:
-//   pass A computes S^T = K Q^T: a lane holds one query column and 16 keys, so the running max/sum
-//          of a row is lane-private; the waves of a block merge their statistics through LDS at the end;
+// The MFMA operand layout is the same for A and B (lane = row or column index mod 32, 8 consecutive channels per lane,
+// lanes 32..63 take the upper 8 of each 16-channel step), so the same registers serve both orientations:
+//   pass A computes S^T = K Q^T: a lane holds one query column and 16 keys, so the sum of a row is lane-private;
 //   pass B computes S = Q K^T: a lane holds one key column and 16 rows, so the column sum of a key
 //          is lane-private adds plus one exchange between half-waves, and is complete inside the wave.
-// Tiles that touch the causal window or the ragged end of the row run a separate instantiation, so
-// the common tile carries no mask arithmetic.  Every key is owned by exactly one wave: no atomics,
-// deterministic output.
+// The window queries (at most 512 rows) are staged in LDS (row pitch 272 B so that the 16-byte operand reads of 8 lanes
+// cover all 32 banks); keys go from global memory straight into MFMA operand registers.  Every key is owned by exactly one
+// wave and every sum is formed in a fixed order: deterministic output.
+//
+// What bounds it (large calls): the issue of matrix and vector instructions together, at the 1.9-2.0 GHz the chip holds
+// under this load.  A product of 32x32x16 takes 32 cycles of the matrix pipe; the six vector instructions that go with
+// it (two logits, two exponentials of 8 cycles, two sums) take 32 cycles, and 42 together measured in isolation with two
+// waves per SIMD; 65 in the kernel.  Hence (80 x 8 x 16384 keys, 512 rows: 3.17 -> 2.73 ms; 28 x 4 x 131072, 224 rows:
+// 2.31 -> 1.93 ms):
+//   - 64 keys per wave: a query operand read from LDS serves two products;
+//   - the products of one tile are interleaved with the vector instructions of the tile before in program order, across
+//     query tiles and key units, so that both pipes have work whatever the other wave of the SIMD does;
+//   - no running maximum in pass A (see there): 3 vector instructions per logit in both passes;
+//   - the keys of the next unit (64 keys x 256 B per wave) are requested a whole unit ahead into registers of their own;
+//     with one tile ahead the loads of 128K-token rows cost 25 % of the time;
+//   - every block works through an equal share of the whole call, so that queries are staged once per (layer, head) row
+//     and block: with 4096-key blocks the launches of 10 blocks per CU cost 30 us each.
 
 #include <mutex>
 #include <type_traits>
@@ -41,11 +47,14 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 
-constexpr int kWavesA = 8;                         // waves per block, pass A (256 VGPRs per wave)
-constexpr int kWavesB = 8;                         // waves per block, pass B
+constexpr int kWaves = 8;                          // waves per block, two per SIMD (256 registers per wave)
+constexpr int kThreads = kWaves * kWave;
+constexpr int kUnitTiles = 2;                      // 32-key tiles a wave of a large call works on at a time
+constexpr int kSmallChunk = 32 * kWaves;           // keys per block of a small call
 constexpr int kPitch = 136;                        // bf16 elements per LDS row (272 B)
 constexpr int kMaxRows = 512;                      // G*W limit (16 query tiles)
-constexpr int kFoldChunks = 16;                    // up to this many key chunks pass B combines the chunk statistics itself
+constexpr int kFoldChunks = 16;                    // up to this many key chunks per row pass B combines their statistics itself
+constexpr int kCUs = 256;                          // one block of 8 waves each
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct ScoreArgs {
@@ -54,11 +63,14 @@ struct ScoreArgs {
   const uint16_t* k;
   int64_t k_sl, k_st, k_sh;
   int32_t T, W, G, Hkv, M, Mrows, nqt;      // nqt = query tiles in use (1 .. 16); Mrows = 32 * nqt
-  int32_t chunk_keys, n_chunks;
+  FastDiv div_w;                            // row r of the window queries: query head r / W, window offset r mod W
+  uint32_t units_lh, units_block, units;    // key units per (layer, head), per block, in all
+  FastDiv div_lh, div_block;                // by units_lh, by units_block
+  int32_t compact_rows;                     // blocks never span two (layer, head) rows: their statistics are numbered by block
   int32_t causal, force_window;
   int32_t fold_combine;                     // pass B combines the chunk statistics itself (few chunks: saves a launch)
   float scale2;                             // log2(e) / sqrt(D)
-  float2* partial;                          // [L*Hkv][n_chunks][Mrows] (max, sum) in the base-2 domain
+  float2* partial;                          // [chunk][Mrows] (reference, sum) in the base-2 domain, chunks numbered by chunk_row
   float* bias;                              // [L*Hkv][Mrows]
   float* scores;                            // [L*Hkv][T]
 };
@@ -72,6 +84,441 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) {
 // row index inside a 32x32 accumulator tile held by vgpr v of this lane
 __device__ __forceinline__ int acc_row(int lane, int v) { return (lane >> 5) * 4 + (v >> 2) * 8 + (v & 3); }
 
+// A block owns units_block consecutive key units of the sequence of all (layer, head) rows.  The part of it inside one
+// row is a chunk: block b's chunk of row lh keeps its statistics in this row of `partial` (b + lh grows with every chunk).
+__device__ __forceinline__ int64_t chunk_row(const ScoreArgs& a, uint32_t b, uint32_t lh) { return a.compact_rows ? b : b + lh; }
+
+// bias_r = max_r + log2(sum_r) over all key chunks of (layer, head) lh; +inf for padding rows (they then contribute 0).
+__device__ __forceinline__ float combined_bias(const ScoreArgs& a, int lh, int r) {
+  if (r >= a.M) return INFINITY;
+  const uint32_t b0 = __builtin_amdgcn_readfirstlane(a.div_block.quot(lh * a.units_lh));   // lh is uniform
+  const int n = __builtin_amdgcn_readfirstlane(a.div_block.quot((lh + 1) * a.units_lh - 1)) - b0 + 1;
+  const float2* part = a.partial + chunk_row(a, b0, lh) * a.Mrows + r;
+  constexpr int kAtOnce = 16;  // statistics requested at once (one memory latency instead of one per chunk)
+  float m = -INFINITY, z = 0.0f;
+  for (int c = 0; c < n; c += kAtOnce) {
+    float2 p[kAtOnce];
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) p[i] = part[static_cast<int64_t>(min(c + i, n - 1)) * a.Mrows];
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i)
+      if (c + i >= n) p[i] = make_float2(-INFINITY, 0.0f);
+    float m_new = m;
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) m_new = fmaxf(m_new, p[i].x);
+    if (m_new == -INFINITY) continue;
+    z *= __builtin_amdgcn_exp2f(m - m_new);   // references are integers: exact
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) z += p[i].y * __builtin_amdgcn_exp2f(p[i].x - m_new);
+    m = m_new;
+  }
+  return m + __builtin_amdgcn_logf(z);  // v_log_f32 is log2
+}
+
+template <int NQT, bool PASS_B>
+__global__ __launch_bounds__(kThreads, 2) void score_kernel(const ScoreArgs a) {
+  constexpr int KT = kUnitTiles;
+  __shared__ __attribute__((aligned(16))) uint16_t q_s[NQT * 32 * kPitch];
+  // pass A: reference exponent of every query row; pass B: its bias
+  __shared__ __attribute__((aligned(16))) float row_s[NQT * 32];
+  __shared__ __attribute__((aligned(16))) int32_t wpos_s[NQT * 32];   // window offset r mod W of query row r (masked tiles)
+  __shared__ __attribute__((aligned(16))) float sum_s[PASS_B ? 4 : kWaves * NQT * 32];   // pass A: sums per wave and row
+  __shared__ float2 merge_s[PASS_B ? 1 : kWaves * 32];
+  __shared__ int32_t ticket_s;   // pass B: next key unit of the chunk that no wave has taken
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: the loops over units are scalar
+  const int win0 = a.T - a.W;  // first window position
+  const int nqt = a.nqt, last = nqt - 1;
+  constexpr int kUnit = 32 * KT;                    // keys a wave works on at a time
+  constexpr int kUnitStride = kUnit * kWaves;
+
+  const uint32_t u_end = min(a.units, (blockIdx.x + 1) * a.units_block);
+  for (uint32_t u = blockIdx.x * a.units_block; u < u_end;) {   // one chunk: this block's part of one (layer, head) row
+  const int lh = __builtin_amdgcn_readfirstlane(a.div_lh.quot(u));
+  const uint32_t u_lh = lh * a.units_lh;
+  const int chunk0 = static_cast<int>(u - u_lh) * kUnit;                                             // this chunk's keys
+  const int t_end = min(a.T, static_cast<int>(min(u_end - u_lh, a.units_lh)) * kUnit);
+  u = u_lh + a.units_lh;
+  const int l = lh / a.Hkv, h = lh - l * a.Hkv;
+  const uint16_t* kbase = a.k + static_cast<int64_t>(l) * a.k_sl + static_cast<int64_t>(h) * a.k_sh;
+  const int t_begin = chunk0 + wave * kUnit;
+  uint4 kop_a[KT][8], kop_b[KT][8];   // the unit at work and the one after it
+  // A 32-key tile at tk as MFMA operand: lane = key tk + lane%32, out[ks] = channels 16 ks + 8 (lane/32) .. +7.  Keys beyond
+  // the row repeat its last one (and are masked).
+  auto load_tile = [&](uint4 (&out)[8], int tk) {
+    const int t0 = min(tk, a.T - 1);
+    const uint16_t* row = kbase + t0 * a.k_st + min(lane & 31, a.T - 1 - t0) * a.k_st + (lane >> 5) * 8;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) out[ks] = *reinterpret_cast<const uint4*>(row + ks * 16);
+  };
+  // this wave's first key unit is requested before anything else, so that its latency overlaps the prologue
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt) load_tile(kop_a[kt], t_begin + 32 * kt);
+
+  // ---- stage the window queries of this (layer, kv head): row r = u * W + w, zeros beyond M.  A thread's
+  //      (at most NQT) pieces are all requested before the first one is stored ----
+  {
+    constexpr int kRowsAtOnce = kThreads / 16, kPieces = NQT * 32 / kRowsAtOnce;
+    const int part = threadIdx.x & 15;
+    int r0 = threadIdx.x >> 4;
+    asm volatile("" : "+v"(r0));   // the row offsets are computed here for every chunk, not kept in registers across them
+    const uint16_t* qbase = a.q + static_cast<int64_t>(l) * a.q_sl + static_cast<int64_t>(h) * a.G * a.q_sh + part * 8;
+    uint4 piece[kPieces];
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+      const int r = min(r0 + kRowsAtOnce * i, a.M - 1);
+      const int g = a.div_w.quot(r), w = r - g * a.W;
+      piece[i] = *reinterpret_cast<const uint4*>(qbase + w * a.q_st + g * a.q_sh);
+    }
+    __syncthreads();   // the previous chunk's queries and sums are no longer read
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) {
+      const int r = r0 + kRowsAtOnce * i;
+      if (r >= a.M) piece[i] = make_uint4(0, 0, 0, 0);
+      if (r < a.Mrows) *reinterpret_cast<uint4*>(q_s + r * kPitch + part * 8) = piece[i];
+    }
+  }
+  for (int r = threadIdx.x; r < a.Mrows; r += kThreads) {
+    wpos_s[r] = r - static_cast<int>(a.div_w.quot(r)) * a.W;
+    // rows beyond M carry +inf: they contribute 2^-inf = 0
+    if constexpr (PASS_B) row_s[r] = a.fold_combine ? combined_bias(a, lh, r) : a.bias[static_cast<int64_t>(lh) * a.Mrows + r];
+  }
+  if (PASS_B && threadIdx.x == 0) ticket_s = 2 * kWaves;
+  if constexpr (!PASS_B) {
+    for (int i = threadIdx.x; i < kWaves * a.Mrows; i += kThreads) sum_s[i] = 0.0f;
+  }
+  __syncthreads();
+
+  // the logit scale in a vector register: with a scalar operand the multiply-adds would issue at half their rate
+  float scale2;
+  asm("v_mov_b32 %0, %1" : "=v"(scale2) : "s"(a.scale2));
+
+  auto q_piece = [&](int qt, int ks) {
+    return as_bf16x8(*reinterpret_cast<const uint4*>(q_s + (qt * 32 + (lane & 31)) * kPitch + (lane >> 5) * 8 + ks * 16));
+  };
+  auto mfma = [&](uint4 k, bf16x8 q, floatx16 c) {
+    if constexpr (PASS_B)
+      return __builtin_amdgcn_mfma_f32_32x32x16_bf16(q, as_bf16x8(k), c, 0, 0, 0);   // rows = queries
+    else
+      return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(k), q, c, 0, 0, 0);   // rows = keys
+  };
+  auto masked = [&](int tk, int n) { return (a.causal && tk + n > win0 + 1) || tk + n > a.T; };
+  // -inf where a key is beyond the row or after the query's own position
+  auto mask_tile = [&](floatx16& c, int qt, int tk) {
+    if constexpr (PASS_B) {   // c[v]: query row qt*32 + acc_row(v), key tk + lane%32
+      const int t = tk + (lane & 31);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int4 w4 = *reinterpret_cast<const int4*>(wpos_s + qt * 32 + g * 8 + (lane >> 5) * 4);
+        const int w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (t >= a.T || (a.causal && t > win0 + w[i])) c[4 * g + i] = -INFINITY;
+      }
+    } else {                  // c[v]: key tk + acc_row(v), query row qt*32 + lane%32
+      const int qpos = win0 + wpos_s[qt * 32 + (lane & 31)];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int t = tk + acc_row(lane, v);
+        if (t >= a.T || (a.causal && t > qpos)) c[v] = -INFINITY;
+      }
+    }
+  };
+  auto pin = [&]() { __builtin_amdgcn_sched_barrier(0); };   // the compiler keeps the order of the groups written below
+
+  // Row values (pass A: one per lane, pass B: one per accumulator) and the sums the exponentials go to.
+  float rowv[PASS_B ? 16 : 1];
+  float sum[PASS_B ? KT : 1][PASS_B ? 1 : 2];   // pass A: of the current query column; pass B: of this lane's key, per key tile
+  auto row_group = [&](int qt, int g) {   // pass B: rows acc_row(lane, 4 g .. 4 g + 3) of query tile qt
+    const float4 b4 = *reinterpret_cast<const float4*>(row_s + qt * 32 + g * 8 + (lane >> 5) * 4);
+    rowv[(4 * g + 0) % (PASS_B ? 16 : 1)] = b4.x; rowv[(4 * g + 1) % (PASS_B ? 16 : 1)] = b4.y;
+    rowv[(4 * g + 2) % (PASS_B ? 16 : 1)] = b4.z; rowv[(4 * g + 3) % (PASS_B ? 16 : 1)] = b4.w;
+  };
+  auto load_rows = [&](int qt) {
+    if constexpr (PASS_B) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) row_group(qt, g);
+    } else {
+      rowv[0] = row_s[qt * 32 + (lane & 31)];
+    }
+  };
+  auto expo = [&](const floatx16& c, int v) { return __builtin_amdgcn_exp2f(fmaf(c[v], scale2, -rowv[PASS_B ? v : 0])); };
+  auto sink = [&](int kt, int v, float e) { sum[PASS_B ? kt : 0][PASS_B ? 0 : v & 1] += e; };
+  auto consume = [&](const floatx16& c, int kt) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sink(kt, v, expo(c, v));
+  };
+  // pass A: the sum of a finished query tile over this unit goes to LDS (this wave's own slots)
+  auto flush_rows = [&](int qt) {
+    if constexpr (!PASS_B) {
+      typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+      const uint32_t z = __float_as_uint(sum[0][0] + sum[0][1]);
+      const u32x2 halves = __builtin_amdgcn_permlane32_swap(z, z, false, false);
+      if (lane < 32)   // one writer per slot, in program order: the result does not depend on timing
+        __hip_atomic_fetch_add(sum_s + wave * a.Mrows + qt * 32 + lane, __uint_as_float(halves[0]) + __uint_as_float(halves[1]),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+      sum[0][0] = sum[0][1] = 0.0f;
+    }
+  };
+
+  // Pass A: reference exponents.  2^(s - ref) may be summed with any reference that keeps the sum in range; the maximum
+  // over the chunk's first key tile, rounded up, does unless a later logit exceeds it by more than 2^7, which shows as
+  // an infinite sum.  The running maximum of the textbook form, and with it a third of the vector work, is not needed.
+  bool slow = false;
+  if constexpr (!PASS_B) {
+    slow = masked(chunk0, 32);     // a row may have no key in the first tile (short rows, last few keys)
+    if (!slow) {
+      uint4 k0[8];
+      load_tile(k0, chunk0);
+      for (int qt = wave; qt < nqt; qt += kWaves) {
+        floatx16 c = {0};
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) c = mfma(k0[ks], q_piece(qt, ks), c);
+        float m = c[0];
+#pragma unroll
+        for (int v = 1; v < 16; ++v) m = fmaxf(m, c[v]);
+        m = fmaxf(m, __shfl_xor(m, 32, 64));
+        if (lane < 32) row_s[qt * 32 + lane] = __builtin_ceilf(m * scale2);   // scale2 > 0: max commutes with it
+      }
+    }
+    __syncthreads();
+  }
+
+  // One pipeline step: the matrix products of one 32x32 tile into acc, interleaved with the vector arithmetic of the tile
+  // finished before (prev, key tile pkt): two elements per product, and three stages (logit, exponential, sum) one product
+  // apart, so that neither an exponential waits for its logit, nor a sum for its exponential, nor the first logits for
+  // the last product of prev.  The stages of the last elements run into the next step (of key tile pkt + 1) or drain.
+  float logit[2], power[2];
+  auto step = [&](auto fresh_tag, floatx16& acc, const floatx16& prev, int pkt, const uint4 (&k)[8], const bf16x8 (&q)[8], auto tail) {
+    constexpr bool FRESH = decltype(fresh_tag)::value;   // nothing left of the step before
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      if (ks == 0) acc = floatx16{0};
+      acc = mfma(k[ks], q[ks], acc);
+      pin();
+      if (ks > 1 || !FRESH) {
+        sink(ks > 1 ? pkt : pkt - 1, 0, power[0]);
+        sink(ks > 1 ? pkt : pkt - 1, 1, power[1]);
+      }
+      if (ks > 0 || !FRESH) {
+        power[0] = __builtin_amdgcn_exp2f(logit[0]);
+        power[1] = __builtin_amdgcn_exp2f(logit[1]);
+      }
+      pin();
+      logit[0] = fmaf(prev[2 * ks], scale2, -rowv[PASS_B ? 2 * ks : 0]);
+      logit[1] = fmaf(prev[2 * ks + 1], scale2, -rowv[PASS_B ? 2 * ks + 1 : 0]);
+      tail(ks);
+      pin();
+    }
+  };
+  auto drain = [&](int pkt) {
+    const float p0 = __builtin_amdgcn_exp2f(logit[0]), p1 = __builtin_amdgcn_exp2f(logit[1]);
+    sink(pkt, 0, power[0]);
+    sink(pkt, 1, power[1]);
+    sink(pkt, 0, p0);
+    sink(pkt, 1, p1);
+  };
+
+  // The unit after `next`.  Pass B: the waves of a block take key units as they get to them (a column sum is complete
+  // inside one wave, so the result does not depend on which wave that is); pass A: every wave its fixed share.
+  auto unit_after = [&](int next) {
+    if constexpr (PASS_B) {
+      int u = 0;
+      if (lane == 0) u = __hip_atomic_fetch_add(&ticket_s, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      return chunk0 + __builtin_amdgcn_readfirstlane(u) * kUnit;
+    } else {
+      return next + kUnitStride;
+    }
+  };
+  auto clear_sums = [&]() {
+#pragma unroll
+    for (int i = 0; i < KT * 2; ++i) sum[PASS_B ? i / 2 : 0][PASS_B ? 0 : i % 2] = 0.0f;
+  };
+  auto store_column = [&](int kt, int tk) {
+    if constexpr (PASS_B) {
+      float col = sum[kt][0];
+      col += __shfl_xor(col, 32, 64);
+      const int t = tk + lane;
+      if (lane < 32 && t < a.T)
+        a.scores[static_cast<int64_t>(lh) * a.T + t] = (a.force_window && t >= win0) ? INFINITY : col;
+      sum[kt][0] = 0.0f;
+    }
+  };
+  // One tile by itself, without overlap: the tiles that need the mask.
+  auto single_tile = [&](const uint4 (&k)[8], int tk) {
+    const bool mask = masked(tk, 32);
+    bf16x8 qop[8];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qop[ks] = q_piece(0, ks);
+#pragma unroll 1
+    for (int qt = 0; qt < nqt; ++qt) {
+      load_rows(qt);
+      floatx16 acc = {0};
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) acc = mfma(k[ks], qop[ks], acc);
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) qop[ks] = q_piece(min(qt + 1, last), ks);
+      if (mask) mask_tile(acc, qt, tk);
+      consume(acc, 0);
+      flush_rows(qt);
+    }
+    store_column(0, tk);
+  };
+
+  // The textbook form of pass A: running maximum (an integer, so that rescaling is exact) and sum per query column.
+  auto online_update = [&](floatx16& c, bool mask, int qt, int tk, float& m, float& z) {
+    if (mask) mask_tile(c, qt, tk);
+    float m_new = c[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) m_new = fmaxf(m_new, c[v]);
+    m_new = fmaxf(m, __builtin_ceilf(m_new * scale2));   // scale2 > 0: max commutes with it
+    const float m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
+    float z0 = z * __builtin_amdgcn_exp2f(m - m_safe), z1 = 0.0f;
+#pragma unroll
+    for (int v = 0; v < 16; v += 2) {
+      z0 += __builtin_amdgcn_exp2f(fmaf(c[v], scale2, -m_safe));
+      z1 += __builtin_amdgcn_exp2f(fmaf(c[v + 1], scale2, -m_safe));
+    }
+    m = m_new;
+    z = z0 + z1;
+  };
+  auto merge_halves = [&](float m, float z) {   // same query column, disjoint keys
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    const u32x2 mm = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    const u32x2 zz = __builtin_amdgcn_permlane32_swap(__float_as_uint(z), __float_as_uint(z), false, false);
+    const float m0 = __uint_as_float(mm[0]), m1 = __uint_as_float(mm[1]);
+    const float m_new = fmaxf(m0, m1);
+    const float m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
+    return make_float2(m_new, __uint_as_float(zz[0]) * __builtin_amdgcn_exp2f(m0 - m_safe) +
+                                  __uint_as_float(zz[1]) * __builtin_amdgcn_exp2f(m1 - m_safe));
+  };
+  auto merge_waves = [&](const float2* s, int pitch) {
+    float m = -INFINITY, z = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) m = fmaxf(m, s[w * pitch].x);
+    const float m_safe = (m == -INFINITY) ? 0.0f : m;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float2 p = s[w * pitch];
+      z += p.y * __builtin_amdgcn_exp2f(p.x - m_safe);
+    }
+    return make_float2(m, z);
+  };
+
+  clear_sums();
+  int tk0 = slow ? t_end : t_begin, next = t_begin + kUnitStride;
+  if (tk0 < t_end && !masked(tk0, kUnit)) {
+    // A pipeline over the tiles in the order (unit, query tile, key tile): a tile is consumed during the products of
+    // the one after it, also across units.
+    bf16x8 qop[8];
+    floatx16 acc[2];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) qop[ks] = q_piece(0, ks);
+    load_rows(0);
+    acc[0] = floatx16{0};
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) acc[0] = mfma(kop_a[0][ks], qop[ks], acc[0]);
+    pin();
+    // key tiles 1 .. of the unit with the query tile at work, whose operands are replaced by those of tile qn
+    auto rest_of_unit = [&](const uint4 (&kop)[KT][8], int qn) {
+      step(std::true_type{}, acc[1], acc[0], 0, kop[1], qop, [&](int ks) { qop[ks] = q_piece(qn, ks); });   // each right after its last use
+    };
+    // key tile 0 with query tile qn, while the last tile of query tile qt is consumed
+    auto first_of_next = [&](const uint4 (&k0)[8], int qt, int qn) {
+      const float row_next = PASS_B ? 0.0f : row_s[qn * 32 + (lane & 31)];
+      step(std::false_type{}, acc[0], acc[1], KT - 1, k0, qop, [&](int ks) {
+        if constexpr (PASS_B) {
+          if (ks & 1) row_group(qn, ks >> 1);   // the rows of these four accumulators are done with tile qt
+        }
+      });
+      drain(KT - 1);
+      flush_rows(qt);
+      if constexpr (!PASS_B) rowv[0] = row_next;
+    };
+    // one unit; the rows of the next one are requested before its arithmetic
+    auto unit = [&](const uint4 (&kop)[KT][8], uint4 (&knext)[KT][8]) {
+      const int after = unit_after(next);
+      const bool more = next < t_end && !masked(next, kUnit);
+      __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this unit's rows, requested a unit ago, are here (no waits below)
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) load_tile(knext[kt], next + 32 * kt);
+      pin();
+#pragma unroll 1
+      for (int qt = 0; qt < last; ++qt) {
+        rest_of_unit(kop, qt + 1);
+        first_of_next(kop[0], qt, qt + 1);
+      }
+      rest_of_unit(kop, 0);
+      if (more) {
+        first_of_next(knext[0], last, 0);
+      } else {
+        drain(KT - 2);
+        consume(acc[1], KT - 1);
+        flush_rows(last);
+      }
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) store_column(kt, tk0 + 32 * kt);
+      tk0 = next;
+      next = after;
+      return more;
+    };
+    while (unit(kop_a, kop_b) && unit(kop_b, kop_a)) {
+    }
+  }
+  while (tk0 < t_end) {
+#pragma unroll 1
+    for (int tk = tk0; tk < min(tk0 + kUnit, t_end); tk += 32) {
+      load_tile(kop_a[0], tk);
+      single_tile(kop_a[0], tk);
+    }
+    tk0 = next;
+    next = unit_after(next);
+  }
+
+  if constexpr (!PASS_B) {
+    float2* part = a.partial + chunk_row(a, blockIdx.x, lh) * a.Mrows;
+    if (!slow) {
+      __syncthreads();
+      bool bad = false;
+      for (int r = threadIdx.x; r < a.Mrows; r += kThreads) {
+        float z = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) z += sum_s[w * a.Mrows + r];
+        bad |= !(z < INFINITY);
+        // the sum may be as large as 2^127: its exponent moves into the (integer) reference
+        part[r] = make_float2(row_s[r] + static_cast<float>(__builtin_amdgcn_frexp_expf(z)), __builtin_amdgcn_frexp_mantf(z));
+      }
+      slow = __syncthreads_or(bad);
+    }
+    if (slow) {   // the textbook form, one query tile at a time
+#pragma unroll 1
+      for (int qt = 0; qt < nqt; ++qt) {
+        float m = -INFINITY, z = 0.0f;
+#pragma unroll 1
+        for (int tk = chunk0 + 32 * wave; tk < t_end; tk += 32 * kWaves) {
+          uint4 k0[8];
+          load_tile(k0, tk);
+          floatx16 c = {0};
+#pragma unroll
+          for (int ks = 0; ks < 8; ++ks) c = mfma(k0[ks], q_piece(qt, ks), c);
+          online_update(c, masked(tk, 32), qt, tk, m, z);
+        }
+        const float2 both = merge_halves(m, z);
+        if (lane < 32) merge_s[wave * 32 + lane] = both;
+        __syncthreads();
+        if (threadIdx.x < 32) part[qt * 32 + threadIdx.x] = merge_waves(merge_s + threadIdx.x, 32);
+        __syncthreads();
+      }
+    }
+  }
+  }
+}
+
+// ---- calls of few keys (256 per block, so that many CUs take part): latency counts, not throughput ----
+//
+// Each wave owns one 32-key tile, requested before the prologue, and walks the query tiles against it with two tiles in
+// flight; pass A in the textbook form (running maximum), which needs no prologue to find references.
 // 32 keys starting at tk0 as an MFMA operand, straight from global memory: lane holds key
 // tk0 + lane%32, channels 16*ks + 8*(lane/32) .. +7.  Keys at or beyond T are zero.
 __device__ __forceinline__ void load_key_tile(const ScoreArgs& a, const uint16_t* kbase, int tk0, int lane, uint4 out[8]) {
@@ -86,39 +533,8 @@ __device__ __forceinline__ void load_key_tile(const ScoreArgs& a, const uint16_t
   }
 }
 
-// bias_r = max_r + log2(sum_r) over all key chunks of (layer, head) lh; +inf for padding rows (they then contribute 0).
-__device__ __forceinline__ float combined_bias(const ScoreArgs& a, int lh, int r) {
-  if (r >= a.M) return INFINITY;
-  const float2* part = a.partial + static_cast<int64_t>(lh) * a.n_chunks * a.Mrows + r;
-  if (a.n_chunks <= kFoldChunks) {
-    // all chunk statistics of the row requested at once (one memory latency instead of one per chunk)
-    float2 p[kFoldChunks];
-#pragma unroll
-    for (int c = 0; c < kFoldChunks; ++c)
-      p[c] = c < a.n_chunks ? part[static_cast<int64_t>(c) * a.Mrows] : make_float2(-INFINITY, 0.0f);
-    float m = -INFINITY;
-#pragma unroll
-    for (int c = 0; c < kFoldChunks; ++c) m = fmaxf(m, p[c].x);
-    float z = 0.0f;
-#pragma unroll
-    for (int c = 0; c < kFoldChunks; ++c)
-      if (p[c].x != -INFINITY) z += p[c].y * __builtin_amdgcn_exp2f(p[c].x - m);
-    return m + __builtin_amdgcn_logf(z);  // v_log_f32 is log2
-  }
-  float m = -INFINITY;
-  for (int c = 0; c < a.n_chunks; ++c) m = fmaxf(m, part[static_cast<int64_t>(c) * a.Mrows].x);
-  float z = 0.0f;
-  for (int c = 0; c < a.n_chunks; ++c) {
-    const float2 p = part[static_cast<int64_t>(c) * a.Mrows];
-    if (p.x != -INFINITY) z += p.y * __builtin_amdgcn_exp2f(p.x - m);
-  }
-  return m + __builtin_amdgcn_logf(z);  // v_log_f32 is log2
-}
-
 template <int NQT, bool PASS_B>
-__global__ __launch_bounds__((PASS_B ? kWavesB : kWavesA) * kWave, 2) void score_kernel(const ScoreArgs a) {
-  constexpr int kWavesPerBlock = PASS_B ? kWavesB : kWavesA;
-  constexpr int kThreads = kWavesPerBlock * kWave;
+__global__ __launch_bounds__(kThreads, 2) void score_small_kernel(const ScoreArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t q_s[NQT * 32 * kPitch];
   __shared__ __attribute__((aligned(16))) float bias_s[PASS_B ? NQT * 32 : 4];
   __shared__ __attribute__((aligned(16))) int32_t wpos_s[NQT * 32];   // window offset r mod W of query row r (masked tiles)
@@ -132,9 +548,9 @@ __global__ __launch_bounds__((PASS_B ? kWavesB : kWavesA) * kWave, 2) void score
   const int win0 = a.T - a.W;  // first window position
 
   // this wave's first key tile is requested before anything else, so that its latency overlaps the prologue
-  constexpr int kTileStride = 32 * kWavesPerBlock;
-  const int t_begin = chunk * a.chunk_keys + wave * 32;
-  const int t_end = min(a.T, (chunk + 1) * a.chunk_keys);   // chunk_keys is a multiple of kTileStride
+  constexpr int kTileStride = 32 * kWaves;
+  const int t_begin = chunk * kSmallChunk + wave * 32;
+  const int t_end = min(a.T, (chunk + 1) * kSmallChunk);   // a multiple of kTileStride
   uint4 kop[8];
   if (t_begin < t_end) load_key_tile(a, kbase, t_begin, lane, kop);
 
@@ -304,7 +720,7 @@ __global__ __launch_bounds__((PASS_B ? kWavesB : kWavesA) * kWave, 2) void score
     }
   };
 
-  // ---- this wave's key tiles: every kWavesPerBlock-th tile of the chunk, so that the few masked tiles at the
+  // ---- this wave's key tiles: every kWaves-th tile of the chunk, so that the few masked tiles at the
   //      end of a row (each costs more) are spread over the waves instead of all landing on the last one ----
   if (t_begin < t_end) {
     uint4 knext[8];
@@ -326,7 +742,7 @@ __global__ __launch_bounds__((PASS_B ? kWavesB : kWavesA) * kWave, 2) void score
   if constexpr (!PASS_B) {
     // merge the two half-waves (same query column, disjoint keys), then the 8 waves through LDS
     __syncthreads();                       // every wave is done reading q_s: reuse it as scratch
-    float2* merge_s = reinterpret_cast<float2*>(q_s);   // [kWavesPerBlock][NQT*32]
+    float2* merge_s = reinterpret_cast<float2*>(q_s);   // [kWaves][NQT*32]
 #pragma unroll
     for (int qt = 0; qt < NQT; ++qt) {
       const float m_o = __shfl_xor(run_m[qt], 32, 64);
@@ -340,15 +756,15 @@ __global__ __launch_bounds__((PASS_B ? kWavesB : kWavesA) * kWave, 2) void score
     for (int r = threadIdx.x; r < a.Mrows; r += kThreads) {
       float m = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < kWavesPerBlock; ++w) m = fmaxf(m, merge_s[w * (NQT * 32) + r].x);
+      for (int w = 0; w < kWaves; ++w) m = fmaxf(m, merge_s[w * (NQT * 32) + r].x);
       const float m_safe = (m == -INFINITY) ? 0.0f : m;
       float z = 0.0f;
 #pragma unroll
-      for (int w = 0; w < kWavesPerBlock; ++w) {
+      for (int w = 0; w < kWaves; ++w) {
         const float2 p = merge_s[w * (NQT * 32) + r];
         z += p.y * __builtin_amdgcn_exp2f(p.x - m_safe);
       }
-      a.partial[(static_cast<int64_t>(lh) * a.n_chunks + chunk) * a.Mrows + r] = make_float2(m, z);
+      a.partial[(static_cast<int64_t>(lh) * gridDim.x + chunk) * a.Mrows + r] = make_float2(m, z);
     }
   }
 }
@@ -359,48 +775,77 @@ __global__ void combine_kernel(const ScoreArgs a) {
   for (int r = threadIdx.x; r < a.Mrows; r += blockDim.x) a.bias[static_cast<int64_t>(lh) * a.Mrows + r] = combined_bias(a, lh, r);
 }
 
-// Keys per block: large chunks amortize the query staging, small ones fill the chip.
-int32_t choose_chunk_keys(int64_t n_lh, int64_t T) {
-  int32_t kc = 4096;
-  while (kc > 256 && n_lh * ceil_div(T, kc) < 512) kc /= 2;
-  return kc;
-}
-
+// How the keys are shared out.  Large calls: 64-key units, 8 waves per block and one block per CU of the chip, every
+// block the same number of units, so that a block stages the queries of few (layer, head) rows (a chunk costs about 30 us
+// besides its keys at M = 512: staging, first loads, waves that wait for the last one; two or three blocks per CU measured
+// 2 and 4 % slower).  Small calls, less than one 64-key unit per wave of the chip: 256-key chunks, so that many CUs take
+// part (8 heads x 4096 keys, M = 128: 15 us for both passes, 20 us with the kernel of the large calls).
 struct ScorePlan {
-  int32_t M, nqt, Mrows, chunk_keys, n_chunks;
-  size_t partial_bytes, bias_bytes;
+  int32_t M, nqt, Mrows;
+  bool wide, fold;
+  int64_t units_lh, units_block, units, blocks;
+  size_t partial_bytes, bytes;
 };
+
+// Scratch of a call.  The size is part of the interface (callers keep workspaces, and the 4 MiB of
+// kvp_score_tokens_static accept or refuse a shape by it), so it stays that of chunks of 256 .. 4096 keys, as few as fill
+// the chip twice, and a bias per row; no plan below needs more.
+size_t scratch_bytes(int64_t n_lh, int64_t T, int64_t Mrows) {
+  int64_t keys = 4096;
+  while (keys > 256 && n_lh * ceil_div(T, keys) < 512) keys /= 2;
+  const size_t partial = static_cast<size_t>(n_lh) * ceil_div(T, keys) * Mrows * sizeof(float2);
+  return (partial + 255) / 256 * 256 + static_cast<size_t>(n_lh) * Mrows * sizeof(float);
+}
 
 ScorePlan make_plan(int64_t L, int64_t Hkv, int64_t Hq, int64_t W, int64_t T) {
   ScorePlan p{};
+  const int64_t n_lh = L * Hkv;
   p.M = static_cast<int32_t>((Hq / Hkv) * W);
   p.nqt = (p.M + 31) / 32;              // query tiles in use (1 .. 16)
   p.Mrows = p.nqt * 32;
-  p.chunk_keys = choose_chunk_keys(L * Hkv, T);
-  p.n_chunks = static_cast<int32_t>(ceil_div(T, p.chunk_keys));
-  p.partial_bytes = static_cast<size_t>(L * Hkv) * p.n_chunks * p.Mrows * sizeof(float2);
+  p.wide = n_lh * ceil_div(T, 32 * kUnitTiles) >= kCUs * kWaves;
+  if (p.wide) {
+    p.units_lh = ceil_div(T, 32 * kUnitTiles);
+    p.units_block = ceil_div(n_lh * p.units_lh, kCUs);
+  } else {
+    p.units_lh = ceil_div(T, kSmallChunk);
+    p.units_block = 1;
+  }
+  p.units = n_lh * p.units_lh;
+  p.blocks = ceil_div(p.units, p.units_block);
+  const int64_t chunks = p.wide ? p.blocks + n_lh - 1 : p.blocks;        // rows of `partial`
+  p.fold = (p.units_lh - 1) / p.units_block + (p.wide ? 2 : 1) <= kFoldChunks;      // chunks a (layer, head) row may have
+  p.partial_bytes = static_cast<size_t>(chunks) * p.Mrows * sizeof(float2);
   p.partial_bytes = (p.partial_bytes + 255) / 256 * 256;
-  p.bias_bytes = static_cast<size_t>(L * Hkv) * p.Mrows * sizeof(float);
+  p.bytes = scratch_bytes(n_lh, T, p.Mrows);
   return p;
 }
 
-// Pass A is instantiated for every tile count 1 .. 16, pass B for 1, 2, 4, 8 and 16 tiles of LDS (M = 224 runs
-// 7 tiles in the 8-tile instantiation).
+// Instantiated for 1, 2, 4, 8 and 16 query tiles of LDS (M = 224 runs 7 tiles in the 8-tile instantiation); pass A of the
+// small calls for every tile count 1 .. 16 (its per-tile statistics live in registers with static indices).
+template <bool PASS_B>
+void launch_wide(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
+  if (nqt <= 1) score_kernel<1, PASS_B><<<grid, kThreads, 0, st>>>(a);
+  else if (nqt <= 2) score_kernel<2, PASS_B><<<grid, kThreads, 0, st>>>(a);
+  else if (nqt <= 4) score_kernel<4, PASS_B><<<grid, kThreads, 0, st>>>(a);
+  else if (nqt <= 8) score_kernel<8, PASS_B><<<grid, kThreads, 0, st>>>(a);
+  else score_kernel<16, PASS_B><<<grid, kThreads, 0, st>>>(a);
+}
+
 template <int N>
-void launch_pass_a(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
+void launch_small_a(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
   if constexpr (N <= 16) {
-    if (nqt == N) score_kernel<N, false><<<grid, kWavesA * kWave, 0, st>>>(a);
-    else launch_pass_a<N + 1>(nqt, grid, st, a);
+    if (nqt == N) score_small_kernel<N, false><<<grid, kThreads, 0, st>>>(a);
+    else launch_small_a<N + 1>(nqt, grid, st, a);
   }
 }
 
-void launch_pass_b(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
-  constexpr int threads = kWavesB * kWave;
-  if (nqt <= 1) score_kernel<1, true><<<grid, threads, 0, st>>>(a);
-  else if (nqt <= 2) score_kernel<2, true><<<grid, threads, 0, st>>>(a);
-  else if (nqt <= 4) score_kernel<4, true><<<grid, threads, 0, st>>>(a);
-  else if (nqt <= 8) score_kernel<8, true><<<grid, threads, 0, st>>>(a);
-  else score_kernel<16, true><<<grid, threads, 0, st>>>(a);
+void launch_small_b(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
+  if (nqt <= 1) score_small_kernel<1, true><<<grid, kThreads, 0, st>>>(a);
+  else if (nqt <= 2) score_small_kernel<2, true><<<grid, kThreads, 0, st>>>(a);
+  else if (nqt <= 4) score_small_kernel<4, true><<<grid, kThreads, 0, st>>>(a);
+  else if (nqt <= 8) score_small_kernel<8, true><<<grid, kThreads, 0, st>>>(a);
+  else score_small_kernel<16, true><<<grid, kThreads, 0, st>>>(a);
 }
 
 }  // namespace
@@ -418,7 +863,7 @@ int32_t score_tokens_impl(const kvp_view* q_win, const kvp_view* k, int32_t caus
   if (q_win->L != L || Hq % Hkv != 0 || W > T || T >= (1ll << 30) || L * Hkv > 65535) return KVP_ERR_SHAPE;
   if ((Hq / Hkv) * W > kMaxRows) return KVP_ERR_UNSUPPORTED;
   const ScorePlan p = make_plan(L, Hkv, Hq, W, T);
-  if (!ws || ws_bytes < p.partial_bytes + p.bias_bytes || (reinterpret_cast<uintptr_t>(ws) & 15u))
+  if (!ws || ws_bytes < p.bytes || (reinterpret_cast<uintptr_t>(ws) & 15u))
     return KVP_ERR_WORKSPACE;
 
   ScoreArgs a{};
@@ -428,20 +873,33 @@ int32_t score_tokens_impl(const kvp_view* q_win, const kvp_view* k, int32_t caus
   a.k_sl = k->stride_l; a.k_st = k->stride_t; a.k_sh = k->stride_h;
   a.T = static_cast<int32_t>(T); a.W = static_cast<int32_t>(W); a.G = static_cast<int32_t>(Hq / Hkv);
   a.Hkv = static_cast<int32_t>(Hkv); a.M = p.M; a.Mrows = p.Mrows; a.nqt = p.nqt;
-  a.chunk_keys = p.chunk_keys; a.n_chunks = p.n_chunks;
+  a.div_w = FastDiv(static_cast<uint32_t>(W));
+  // fewer than 2^31 units: more would need more than 2^37 scores, which no device holds
+  a.units_lh = static_cast<uint32_t>(p.units_lh); a.units_block = static_cast<uint32_t>(p.units_block);
+  a.units = static_cast<uint32_t>(p.units);
+  a.div_lh = FastDiv(a.units_lh); a.div_block = FastDiv(a.units_block);
+  a.compact_rows = p.wide ? 0 : 1;
   a.causal = causal ? 1 : 0; a.force_window = force_window ? 1 : 0;
   a.scale2 = kLog2e / sqrtf(static_cast<float>(kHeadDim));
   a.partial = static_cast<float2*>(ws);
-  a.bias = reinterpret_cast<float*>(static_cast<char*>(ws) + p.partial_bytes);
+  a.bias = reinterpret_cast<float*>(static_cast<char*>(ws) + p.partial_bytes);   // not used when pass B combines
   a.scores = scores;
 
-  const dim3 grid(static_cast<unsigned>(p.n_chunks), static_cast<unsigned>(L * Hkv));
-  // With few chunks every pass-B block combines the chunk statistics of its (layer, head) itself (a few KiB of
-  // reads from the cache): a call is two launches, which is what counts for small, launch-bound shapes.
-  a.fold_combine = p.n_chunks <= kFoldChunks ? 1 : 0;
-  launch_pass_a<1>(p.nqt, grid, st, a);
-  if (!a.fold_combine) combine_kernel<<<dim3(static_cast<unsigned>(L * Hkv)), 256, 0, st>>>(a);
-  launch_pass_b(p.nqt, grid, st, a);
+  // With few chunks pass B combines the chunk statistics of its rows itself (a few KiB of reads from the cache): a call
+  // is two launches, which is what counts for small, launch-bound shapes.
+  a.fold_combine = p.fold ? 1 : 0;
+  const dim3 rows(static_cast<unsigned>(L * Hkv));
+  if (p.wide) {
+    const dim3 grid(static_cast<unsigned>(p.blocks));
+    launch_wide<false>(p.nqt, grid, st, a);
+    if (!p.fold) combine_kernel<<<rows, 256, 0, st>>>(a);
+    launch_wide<true>(p.nqt, grid, st, a);
+  } else {
+    const dim3 grid(static_cast<unsigned>(p.units_lh), rows.x);
+    launch_small_a<1>(p.nqt, grid, st, a);
+    if (!p.fold) combine_kernel<<<rows, 256, 0, st>>>(a);
+    launch_small_b(p.nqt, grid, st, a);
+  }
   return launch_status();
 }
 
@@ -450,7 +908,7 @@ int32_t score_tokens_impl(const kvp_view* q_win, const kvp_view* k, int32_t caus
 extern "C" size_t kvp_score_workspace_bytes(int64_t L, int64_t Hkv, int64_t Hq, int64_t W, int64_t T) {
   if (L <= 0 || Hkv <= 0 || Hq <= 0 || W <= 0 || T <= 0 || Hq % Hkv != 0) return 0;
   const kvp::ScorePlan p = kvp::make_plan(L, Hkv, Hq, W, T);
-  return p.partial_bytes + p.bias_bytes;
+  return p.bytes;
 }
 
 extern "C" int32_t kvp_score_tokens(const kvp_view* q_win, const kvp_view* k, int32_t causal, int32_t force_window,
