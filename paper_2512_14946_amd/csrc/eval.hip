@@ -12,11 +12,11 @@
 //      tokens that enter the keep-set at the j-th smallest keep_k.  One kernel turns the lists into
 //      a permutation of the tokens ordered by shell;
 //   3. ONE stream per distinct (bits, group): attention of the window rows over the tokens in shell
-//      order with K and V quantized and dequantized on the fly; at every shell boundary the running
-//      output is the output of that keep level and is stored.  Every candidate keep level of a codec
-//      therefore costs one pass over its largest keep-set instead of one pass each.  The 16-bit
-//      stream also walks the tokens no level keeps: its last state is O_full (the reference);
-//   4. sum (O_level - O_full)^2 per stored output and sum O_full^2 (compare kernel);
+//      order with K and V quantized and dequantized on the fly, one block per shell (segment) and 128 rows.
+//      The output of a keep level is the combination of its segments, so every candidate keep level of a
+//      codec costs one pass over its largest keep-set instead of one pass each.  The 16-bit
+//      stream also walks the tokens no level keeps: all its segments together are O_full (the reference);
+//   4. the segments combined level by level, sum (O_level - O_full)^2 and sum O_full^2 (compare kernel);
 //   5. a reduction in a fixed order (deterministic) to loss[] and partial[].
 //
 // The attention kernel (step 3) walks the tokens in tiles of 32.  Per tile: 256 threads
@@ -40,6 +40,8 @@
 //     registers: the tokens a lane holds after the logits tile are exactly the tokens its P^T
 //     operand must hold, given a matching (permuted) token order in the V-hat^T operand, and the
 //     per-query rescaling is lane-private.
+
+#include <algorithm>
 
 #include "kvp_internal.h"
 #include "quant_device.h"
@@ -83,12 +85,12 @@ struct EvalArgs {
   int32_t level_k[kMaxLevels];           // ascending
   const int32_t* level_idx[kMaxLevels];  // [L*Hkv][k] ascending keep list, or null when k == T
   StreamDesc streams[kMaxCfgs + 1];      // + a hidden 16-bit stream when no configuration asks for one
-  int32_t ref_stream;                    // the 16-bit stream: it walks all T tokens and doubles as the reference
+  int32_t ref_stream;                    // the 16-bit stream: it walks all T tokens and is the reference
   uint8_t cfg_stream[kMaxCfgs], cfg_level[kMaxCfgs];
   uint8_t* shell;   // [L*Hkv][T] scratch: index of the first keep level that holds the token
   int32_t* order;   // [L*Hkv][T] tokens ordered by shell, ascending inside a shell
-  float* o_levels;  // [L*Hkv][RB][n_streams][n_levels + 1][128 x 128]: normalized output of a stream at each level
-                    // (slot n_levels: the reference's state after all T tokens)
+  float* o_parts;   // [L*Hkv][RB][out_slot][128 x 128]: normalized attention of a stream over one segment of the tokens
+  float2* stats;    // [L*Hkv][RB][n_streams][n_levels + 1][128]: (running maximum, row sum) behind each of them
   float* den_part;  // [L*Hkv][RB]
   float* num_part;  // [L*Hkv][RB][n_streams][n_levels]
   double* layer_part;  // [L][n_cfgs][2] scratch of the final reduction
@@ -145,15 +147,6 @@ __device__ __forceinline__ uint4 fake_quant8(const uint4 raw, int bits, int grou
   }
   return make_uint4(pack_bf16x2(q[0] * scale, q[1] * scale), pack_bf16x2(q[2] * scale, q[3] * scale),
                     pack_bf16x2(q[4] * scale, q[5] * scale), pack_bf16x2(q[6] * scale, q[7] * scale));
-}
-
-__device__ __forceinline__ float block_sum(float v, float* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
 }
 
 // Tokens of one (layer, kv head) ordered by shell.  One 1024-thread block per row: the keep lists
@@ -249,30 +242,42 @@ __device__ __forceinline__ void stage_v_transposed(uint16_t* vt_s, uint4 vp, int
   *reinterpret_cast<uint2*>(vt_s + vt_row(part * 8 + 2 * j + 1) * kVtPitch + col) = odd;
 }
 
-// Work item of a block.  The streams of one (layer, kv head, row block) read the same K and V tiles, in the same
-// order and at about the same pace.  Workgroups go to the 8 XCDs (each with its own L2) round-robin by linear
-// id, so block b serves item (b mod 8) * ceil(items / 8) + b / 8: every XCD gets a contiguous run of items, with
-// the stream index varying fastest, and the streams of a cell find each other's tiles in their XCD's L2.
+// Segments of the token order end at the keep levels; one more, walked by the 16-bit stream only, holds the tokens no
+// level keeps.  A block attends over one segment; level j of a stream is the combination of its segments 0 .. j.
+__device__ __forceinline__ bool extra_segment(const EvalArgs& a) { return a.level_k[a.n_levels - 1] < a.T; }
+__device__ __forceinline__ int64_t out_slot(const EvalArgs& a, int64_t cell, int stream, int seg) {
+  return cell * (a.n_streams * a.n_levels + 1) + (seg == a.n_levels ? a.n_streams * a.n_levels : stream * a.n_levels + seg);
+}
+__device__ __forceinline__ float2* stats_of(const EvalArgs& a, int64_t cell, int stream, int seg) {
+  return a.stats + ((cell * a.n_streams + stream) * (a.n_levels + 1) + seg) * kRowsPerBlock;
+}
+
+// Work item of a block: item `index` of a cell (row block of a layer and kv head), per_cell of them.  The streams of one
+// cell read the same K and V tiles, in the same order and at about the same pace.  Workgroups go to the 8 XCDs (each with
+// its own L2) round-robin by linear id, so block b serves item (b mod 8) * ceil(items / 8) + b / 8: every XCD gets a
+// contiguous run of items, with the stream index varying fastest, and the streams of a cell find each other's tiles in
+// their XCD's L2.
 struct WorkItem {
-  int rb, lh, stream;
+  int rb, lh, index;
   bool valid;
 };
 constexpr int kXcds = 8;
-__device__ __forceinline__ WorkItem work_item(const EvalArgs& a) {
-  const int items = a.RB * a.L * a.Hkv * a.n_streams;
+__device__ __forceinline__ WorkItem work_item(const EvalArgs& a, int per_cell) {
+  const int items = a.RB * a.L * a.Hkv * per_cell;
   const int per_xcd = (items + kXcds - 1) / kXcds;
   const int w = static_cast<int>(blockIdx.x % kXcds) * per_xcd + static_cast<int>(blockIdx.x / kXcds);
   WorkItem it;
   it.valid = static_cast<int>(blockIdx.x / kXcds) < per_xcd && w < items;
-  it.stream = w % a.n_streams;
-  const int cell = w / a.n_streams;
+  it.index = w % per_cell;
+  const int cell = w / per_cell;
   it.rb = cell % a.RB;
   it.lh = cell / a.RB;
   return it;
 }
 
-// One launch covers every stream; the 16-bit stream also walks the tokens no keep level holds and so ends
-// as the reference O_full.  Outputs are compared afterwards (compare_kernel).
+// One launch covers every segment of every stream, a block for each: a context of 8 layers x 4 kv heads (224 rows, ten
+// streams) is 640 blocks with whole streams, one and a quarter times what the chip holds at once, and 2560 with segments
+// (measured with matrix-core P.V: 0.92 -> 0.71 ms).  The outputs are combined and compared afterwards (compare_kernel).
 // PV: how the P.V product is formed (kPvDot2: packed fp16 pairs on the vector ALU; kPvMatrix: two-term bf16 split
 // of P on the matrix cores; kPvFp32: fp32 on the vector ALU).
 template <int PV>
@@ -295,12 +300,15 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5;
-  const WorkItem item = work_item(a);
+  const int extra = extra_segment(a) ? 1 : 0;
+  const WorkItem item = work_item(a, a.n_streams * a.n_levels + extra);
   if (!item.valid) return;
-  const int rb = item.rb, lh = item.lh, stream = item.stream;
+  const int rb = item.rb, lh = item.lh;
+  // the segment nobody keeps may be the longest: first
+  const int stream = item.index < extra ? a.ref_stream : (item.index - extra) % a.n_streams;
+  const int seg = item.index < extra ? a.n_levels : (item.index - extra) / a.n_streams;
   const int l = lh / a.Hkv, h = lh - l * a.Hkv;
   const int bits = a.streams[stream].bits, group = a.streams[stream].group;
-  const bool is_ref = stream == a.ref_stream;
   const int32_t* order = a.order + static_cast<int64_t>(lh) * a.T;
   const uint16_t* kbase = a.k + static_cast<int64_t>(l) * a.k_sl + static_cast<int64_t>(h) * a.k_sh;
   const uint16_t* vbase = a.v + static_cast<int64_t>(l) * a.v_sl + static_cast<int64_t>(h) * a.v_sh;
@@ -326,38 +334,20 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
 
   // Output accumulators, 64 per thread.
   //   matrix cores: O^T of this wave's 32 queries, o[16 ct + v] = channel 32 ct + acc_row(lane, v) of query lane%32
-  //   vector ALU:   an 8x8 tile, o[8 i + j] = row {4ty.., 64+4ty..}[i], channel {4tx.., 64+4tx..}[j]
+  //   vector ALU:   an 8x8 tile, o[8 i + j] = row prow + i (of this wave's 32), channel {4tx.., 64+4tx..}[j]
   float o[64];
 #pragma unroll
   for (int i = 0; i < 64; ++i) o[i] = 0.0f;
-  const int ty = tid >> 4, tx = tid & 15;
-  // this block's output slots; each thread's 64 values of a level are contiguous
-  float* levels_out = a.o_levels + (((static_cast<int64_t>(lh) * a.RB + rb) * a.n_streams + stream) * (a.n_levels + 1)) *
-                                       (kRowsPerBlock * kHeadDim) + tid * 64;
+  const int tx = lane & 15, prow = wave * 32 + 8 * (lane >> 4);
+  const int seg_begin = seg > 0 ? a.level_k[seg - 1] : 0, seg_end = seg < a.n_levels ? a.level_k[seg] : a.T;
 
-  // segments end at the keep levels (tiles never straddle a level boundary, so the state at a
-  // boundary is exactly that level's attention).  The 16-bit stream also walks the tokens no level
-  // keeps (one more segment), which makes its final state the reference.
-  const int n_seg = a.n_levels + ((is_ref && a.level_k[a.n_levels - 1] < a.T) ? 1 : 0);
-  auto seg_end_of = [&](int sg) { return sg < a.n_levels ? a.level_k[sg] : a.T; };
-
-  // Tile cursor: tile = positions [pos, min(pos + 32, end)) of segment seg.  Global loads run ahead of
-  // the arithmetic: the permutation entries of a tile are fetched two tiles early and its K and V rows
-  // one tile early, so neither of the two dependent latencies sits between two tiles.
-  struct Cursor { int pos, seg, end; };
-  auto advance = [&](Cursor c) {
-    c.pos += kTile;
-    if (c.pos >= c.end && c.seg < n_seg) {
-      c.pos = c.end;
-      c.seg += 1;
-      if (c.seg < n_seg) c.end = seg_end_of(c.seg);
-    }
-    return c;
-  };
+  // Tile = positions [pos, min(pos + 32, seg_end)) of the token order.  Global loads run ahead of the arithmetic: the
+  // permutation entries of a tile are fetched two tiles early and its K and V rows one tile early, so neither of the two
+  // dependent latencies sits between two tiles.
   const int tk_a = tid >> 4, tk_b = (tid + kThreads) >> 4, part = tid & 15;   // this thread's two staging slots
-  auto load_token = [&](const Cursor& c, int tk) {
+  auto load_token = [&](int pos, int tk) {
     int t = 0x7fffffff;  // beyond every query position: masked
-    if (c.seg < n_seg && c.pos + tk < c.end) t = min(max(order[c.pos + tk], 0), a.T - 1);
+    if (pos + tk < seg_end) t = min(max(order[pos + tk], 0), a.T - 1);
     return t;
   };
   auto load_row = [&](const uint16_t* base, int64_t stride, int t) {
@@ -392,17 +382,14 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
     has_window |= (t >= win0);   // window tokens and padding slots of a ragged tile need the mask
   };
 
-  Cursor cur{0, 0, seg_end_of(0)};
-  Cursor nxt = advance(cur);
-  int t_a = load_token(cur, tk_a), t_b = load_token(cur, tk_b);
+  int t_a = load_token(seg_begin, tk_a), t_b = load_token(seg_begin, tk_b);
   uint4 k_a = load_row(kbase, a.k_st, t_a), v_a = load_row(vbase, a.v_st, t_a);
   uint4 k_b = load_row(kbase, a.k_st, t_b), v_b = load_row(vbase, a.v_st, t_b);
-  int tn_a = load_token(nxt, tk_a), tn_b = load_token(nxt, tk_b);
+  int tn_a = load_token(seg_begin + kTile, tk_a), tn_b = load_token(seg_begin + kTile, tk_b);
 
   if (tid == 0) mask_s[0] = mask_s[1] = 0;
   int parity = 0;
-  while (cur.seg < n_seg) {
-    const int seg = cur.seg;
+  for (int pos = seg_begin; pos < seg_end; pos += kTile) {
     {
       __syncthreads();  // the previous tile's LDS is no longer read
       if (tid == 0) mask_s[parity ^ 1] = 0;   // the previous tile's flag has been read by everybody
@@ -412,17 +399,14 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
       stage(tk_b, t_b, k_b, v_b);
       if (has_window) mask_s[parity] = 1;     // rare; every writer stores the same value
       // ---- run ahead: rows of the next tile, permutation entries of the one after ----
-      const Cursor nn = advance(nxt);
       t_a = tn_a;
       t_b = tn_b;
       k_a = load_row(kbase, a.k_st, t_a);
       v_a = load_row(vbase, a.v_st, t_a);
       k_b = load_row(kbase, a.k_st, t_b);
       v_b = load_row(vbase, a.v_st, t_b);
-      tn_a = load_token(nn, tk_a);
-      tn_b = load_token(nn, tk_b);
-      cur = nxt;
-      nxt = nn;
+      tn_a = load_token(pos + 2 * kTile, tk_a);
+      tn_b = load_token(pos + 2 * kTile, tk_b);
       __syncthreads();                         // publishes the stage and the flag
       const bool need_mask = mask_s[parity] != 0;
       parity ^= 1;
@@ -515,10 +499,13 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
         }
         run_z = run_z * alpha + zsum;
         if (lane < 32) alpha_s[rloc] = alpha;
-        __syncthreads();
+        // the probabilities and factors of this wave's rows are read by this wave only: no barrier
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         // ---- O = O * alpha + P V-hat on the vector ALU, fp32 accumulation ----
-        const float4 a0 = *reinterpret_cast<const float4*>(alpha_s + 4 * ty);
-        const float4 a1 = *reinterpret_cast<const float4*>(alpha_s + 64 + 4 * ty);
+        const float4 a0 = *reinterpret_cast<const float4*>(alpha_s + prow);
+        const float4 a1 = *reinterpret_cast<const float4*>(alpha_s + prow + 4);
         const float al[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
         bool moved = false;
 #pragma unroll
@@ -532,8 +519,8 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
         if constexpr (PV_DOT2) {
 #pragma unroll 4
           for (int tp = 0; tp < kTile / 2; ++tp) {
-            const uint4 p0 = *reinterpret_cast<const uint4*>(p2_s + tp * kRowsPerBlock + 4 * ty);
-            const uint4 p1 = *reinterpret_cast<const uint4*>(p2_s + tp * kRowsPerBlock + 64 + 4 * ty);
+            const uint4 p0 = *reinterpret_cast<const uint4*>(p2_s + tp * kRowsPerBlock + prow);
+            const uint4 p1 = *reinterpret_cast<const uint4*>(p2_s + tp * kRowsPerBlock + prow + 4);
             const uint4 v0 = *reinterpret_cast<const uint4*>(v2_s + tp * kHeadDim + 4 * tx);
             const uint4 v1 = *reinterpret_cast<const uint4*>(v2_s + tp * kHeadDim + 64 + 4 * tx);
             const uint32_t pr[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
@@ -547,8 +534,8 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
         } else {
 #pragma unroll 4
           for (int tk = 0; tk < kTile; ++tk) {
-            const float4 p0 = *reinterpret_cast<const float4*>(p_s + tk * kRowsPerBlock + 4 * ty);
-            const float4 p1 = *reinterpret_cast<const float4*>(p_s + tk * kRowsPerBlock + 64 + 4 * ty);
+            const float4 p0 = *reinterpret_cast<const float4*>(p_s + tk * kRowsPerBlock + prow);
+            const float4 p1 = *reinterpret_cast<const float4*>(p_s + tk * kRowsPerBlock + prow + 4);
             const float4 v0 = *reinterpret_cast<const float4*>(v_s + tk * kHeadDim + 4 * tx);
             const float4 v1 = *reinterpret_cast<const float4*>(v_s + tk * kHeadDim + 64 + 4 * tx);
             const float pr[8] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w};
@@ -561,86 +548,137 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
         }
       }
     }
-    if (cur.seg == seg) continue;                      // more tiles in this segment
-
-    // ---- end of a segment: store the normalized output of this level ----
-    float inv[8];      // 1 / row sum of the rows this thread's accumulators belong to
-    if constexpr (PV_MFMA) {
-      const float one = 1.0f / (run_z + __shfl_xor(run_z, 32, 64));
-#pragma unroll
-      for (int i = 0; i < 8; ++i) inv[i] = one;
-    } else {
-      const float z = run_z + __shfl_xor(run_z, 32, 64);
-      __syncthreads();
-      if (lane < 32) z_s[wave * 32 + lane] = z;
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < 8; ++i) inv[i] = 1.0f / z_s[(i < 4) ? 4 * ty + i : 64 + 4 * ty + (i - 4)];
-    }
-    float4* cell = reinterpret_cast<float4*>(levels_out + static_cast<int64_t>(seg) * (kRowsPerBlock * kHeadDim));
-#pragma unroll
-    for (int i = 0; i < 8; ++i)       // accumulators 8 i .. 8 i + 7 share a row in the vector-ALU layout
-#pragma unroll
-      for (int jh = 0; jh < 2; ++jh) {
-        const int e = 8 * i + 4 * jh;
-        cell[e >> 2] = make_float4(o[e] * inv[i], o[e + 1] * inv[i], o[e + 2] * inv[i], o[e + 3] * inv[i]);
-      }
-    // the reference state is the last one the 16-bit stream reaches; keep it in the extra slot as well
-    if (is_ref && seg == n_seg - 1 && seg != a.n_levels) {
-      float4* last = reinterpret_cast<float4*>(levels_out + static_cast<int64_t>(a.n_levels) * (kRowsPerBlock * kHeadDim));
-#pragma unroll
-      for (int q4 = 0; q4 < 16; ++q4) last[q4] = cell[q4];
-    }
   }
+
+  // ---- the normalized output of this segment and its statistics; a row that sees none of its tokens has sum 0 ----
+  const int64_t cell = static_cast<int64_t>(lh) * a.RB + rb;
+  const float z = run_z + __shfl_xor(run_z, 32, 64);
+  if (lane < 32) stats_of(a, cell, stream, seg)[wave * 32 + lane] = make_float2(run_m, z);
+  float inv[8];      // 1 / row sum of the rows this thread's accumulators belong to
+  if constexpr (PV_MFMA) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) inv[i] = z == 0.0f ? 0.0f : 1.0f / z;
+  } else {
+    if (lane < 32) z_s[wave * 32 + lane] = z == 0.0f ? 0.0f : 1.0f / z;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) inv[i] = z_s[prow + i];
+  }
+  // each thread's 64 values are contiguous
+  float4* out = reinterpret_cast<float4*>(a.o_parts + out_slot(a, cell, stream, seg) * (kRowsPerBlock * kHeadDim) + tid * 64);
+#pragma unroll
+  for (int i = 0; i < 8; ++i)       // accumulators 8 i .. 8 i + 7 share a row in the vector-ALU layout
+#pragma unroll
+    for (int jh = 0; jh < 2; ++jh) {
+      const int e = 8 * i + 4 * jh;
+      out[e >> 2] = make_float4(o[e] * inv[i], o[e + 1] * inv[i], o[e + 2] * inv[i], o[e + 3] * inv[i]);
+    }
 }
 
-// Squared distances between every stored level of every stream and the reference, and the reference's own
-// squared norm; one block per (row block, layer x head, stream).  A stored output is 256 runs of 64 floats (one
-// run per thread of attention_kernel); here consecutive threads read consecutive 16-byte pieces, and the
-// query row a piece belongs to follows from its position.
+// Squared distances between every level of every stream and the reference, and the reference's own squared norm; one
+// block per (row block, layer x head) and spb streams, which share the merged reference in registers.  The level outputs
+// come from the segments by the usual merge of attention partials: O <- O 2^(M - M') + O_seg z_seg 2^(m_seg - M'), divided
+// by the sum merged the same way; the reference goes through the same steps, so that the identity candidate differs from
+// it by exactly nothing.  A stored output is 256 runs of 64 floats (one run per thread of attention_kernel); here
+// consecutive threads read consecutive 16-byte pieces, and the query row a piece belongs to follows from its position.
+// Bound by the reads of the stored outputs: 40 levels of 256 cells in 126 us (5.9 TB/s of the 0.74 GB read; a block per
+// stream that merges the reference for itself: 280 us).
+constexpr int kCompareThreads = 1024;
+constexpr int kMaxStreamsPerBlock = 5;
+struct MergeFactors { float keep, add, inv; };
 template <bool PV_MFMA>
-__global__ __launch_bounds__(kThreads) void compare_kernel(const EvalArgs a) {
-  __shared__ float red_s[4];
-  const int tid = threadIdx.x;
-  const WorkItem item = work_item(a);
+__global__ __launch_bounds__(kCompareThreads, 4) void compare_kernel(const EvalArgs a, int spb) {
+  extern __shared__ MergeFactors factors_s[];   // [spb * n_levels (streams) + n_ref (reference)][128 rows]
+  __shared__ float red_s[kMaxStreamsPerBlock * kMaxLevels + 1][kCompareThreads / kWave];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_groups = (a.n_streams + spb - 1) / spb;
+  const WorkItem item = work_item(a, n_groups);
   if (!item.valid) return;
-  const int rb = item.rb, lh = item.lh, st = item.stream;
-  const int64_t cellrow = static_cast<int64_t>(lh) * a.RB + rb;
-  const int64_t per_level = kRowsPerBlock * kHeadDim;
-  const float4* ref = reinterpret_cast<const float4*>(
-      a.o_levels + ((cellrow * a.n_streams + a.ref_stream) * (a.n_levels + 1) + a.n_levels) * per_level);
-  // piece f = 256 j + tid is piece (f mod 16) of the run of writer thread f / 16 = 16 j + tid / 16
-  const int q4 = tid & 15, i = q4 >> 1;   // accumulators 8 i .. 8 i + 7 of the writer
-  bool live[16];
-  float4 r[16];
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int writer = 16 * j + (tid >> 4);
-    const int ty = writer >> 4;
-    const int rloc = PV_MFMA ? (writer >> 6) * 32 + (writer & 31) : ((i < 4) ? 4 * ty + i : 64 + 4 * ty + (i - 4));
-    live[j] = rb * kRowsPerBlock + rloc < a.M;
-    r[j] = ref[256 * j + tid];
-  }
-  if (st == a.ref_stream) {
-    float sq = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 16; ++j)
-      if (live[j]) sq += r[j].x * r[j].x + r[j].y * r[j].y + r[j].z * r[j].z + r[j].w * r[j].w;
-    const float total = block_sum(sq, red_s);
-    if (tid == 0) a.den_part[cellrow] = total;
-  }
-  for (int lev = 0; lev < a.n_levels; ++lev) {
-    const float4* val =
-        reinterpret_cast<const float4*>(a.o_levels + ((cellrow * a.n_streams + st) * (a.n_levels + 1) + lev) * per_level);
-    float sq = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      const float4 v = val[256 * j + tid];
-      const float dx = v.x - r[j].x, dy = v.y - r[j].y, dz = v.z - r[j].z, dw = v.w - r[j].w;
-      if (live[j]) sq += dx * dx + dy * dy + dz * dz + dw * dw;
+  const int rb = item.rb;
+  const int64_t cell = static_cast<int64_t>(item.lh) * a.RB + rb;
+  const int st0 = item.index * spb, n_st = min(spb, a.n_streams - st0);
+  const int64_t per_slot = kRowsPerBlock * kHeadDim;
+  const int n_ref = a.n_levels + (extra_segment(a) ? 1 : 0);
+  MergeFactors* ref_s = factors_s + spb * a.n_levels * kRowsPerBlock;
+  for (int i = tid; i < (n_st + 1) * kRowsPerBlock; i += kCompareThreads) {
+    const int row = i & (kRowsPerBlock - 1), s = i / kRowsPerBlock;   // s == n_st: the reference
+    const int n = s == n_st ? n_ref : a.n_levels, st = s == n_st ? a.ref_stream : st0 + s;
+    MergeFactors* out = (s == n_st ? ref_s : factors_s + s * a.n_levels * kRowsPerBlock) + row;
+    float m = -INFINITY, z = 0.0f;
+    for (int sg = 0; sg < n; ++sg) {
+      const float2 p = stats_of(a, cell, st, sg)[row];
+      const float m_new = fmaxf(m, p.x), m_safe = m_new == -INFINITY ? 0.0f : m_new;
+      const float keep = __builtin_amdgcn_exp2f(m - m_safe), add = p.y * __builtin_amdgcn_exp2f(p.x - m_safe);
+      z = z * keep + add;
+      m = m_new;
+      out[sg * kRowsPerBlock] = MergeFactors{keep, add, 1.0f / z};
     }
-    const float total = block_sum(sq, red_s);
-    if (tid == 0) a.num_part[(cellrow * a.n_streams + st) * a.n_levels + lev] = total;
+  }
+  __syncthreads();
+  // piece f = 1024 j + tid is piece (f mod 16) of the run of writer thread f / 16
+  constexpr int kPieces = kRowsPerBlock * kHeadDim / 4 / kCompareThreads;
+  const int i = (tid & 15) >> 1;   // accumulators 8 i .. 8 i + 7 of the writer
+  int row[kPieces];
+  bool live[kPieces];
+#pragma unroll
+  for (int j = 0; j < kPieces; ++j) {
+    const int writer = (kCompareThreads / 16) * j + (tid >> 4);
+    row[j] = (writer >> 6) * 32 + (PV_MFMA ? writer & 31 : ((writer >> 4) & 3) * 8 + i);
+    live[j] = rb * kRowsPerBlock + row[j] < a.M;
+  }
+  float4 r[kPieces], o[kPieces];
+  auto merge = [&](float4& acc, const float4 v, const MergeFactors& f) {
+    acc.x = acc.x * f.keep + v.x * f.add; acc.y = acc.y * f.keep + v.y * f.add;
+    acc.z = acc.z * f.keep + v.z * f.add; acc.w = acc.w * f.keep + v.w * f.add;
+  };
+  auto wave_total = [&](float v, int slot) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if (lane == 0) red_s[slot][wave] = v;
+  };
+#pragma unroll
+  for (int j = 0; j < kPieces; ++j) r[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (int sg = 0; sg < n_ref; ++sg) {
+    const float4* val = reinterpret_cast<const float4*>(a.o_parts + out_slot(a, cell, a.ref_stream, sg) * per_slot);
+#pragma unroll
+    for (int j = 0; j < kPieces; ++j) merge(r[j], val[kCompareThreads * j + tid], ref_s[sg * kRowsPerBlock + row[j]]);
+  }
+  float sq = 0.0f;
+#pragma unroll
+  for (int j = 0; j < kPieces; ++j) {
+    const float inv = ref_s[(n_ref - 1) * kRowsPerBlock + row[j]].inv;
+    r[j].x *= inv; r[j].y *= inv; r[j].z *= inv; r[j].w *= inv;
+    if (live[j]) sq += r[j].x * r[j].x + r[j].y * r[j].y + r[j].z * r[j].z + r[j].w * r[j].w;
+  }
+  wave_total(sq, kMaxStreamsPerBlock * kMaxLevels);
+  for (int s = 0; s < n_st; ++s) {
+#pragma unroll
+    for (int j = 0; j < kPieces; ++j) o[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int lev = 0; lev < a.n_levels; ++lev) {
+      const float4* val = reinterpret_cast<const float4*>(a.o_parts + out_slot(a, cell, st0 + s, lev) * per_slot);
+      sq = 0.0f;
+#pragma unroll
+      for (int j = 0; j < kPieces; ++j) {
+        const MergeFactors f = factors_s[(s * a.n_levels + lev) * kRowsPerBlock + row[j]];
+        merge(o[j], val[kCompareThreads * j + tid], f);
+        const float dx = o[j].x * f.inv - r[j].x, dy = o[j].y * f.inv - r[j].y, dz = o[j].z * f.inv - r[j].z, dw = o[j].w * f.inv - r[j].w;
+        if (live[j]) sq += dx * dx + dy * dy + dz * dz + dw * dw;
+      }
+      wave_total(sq, s * kMaxLevels + lev);
+    }
+  }
+  __syncthreads();
+  for (int t = tid; t < n_st * a.n_levels + 1; t += kCompareThreads) {
+    const bool den = t == n_st * a.n_levels;
+    const int s = t / a.n_levels, lev = t % a.n_levels;
+    const float* part = red_s[den ? kMaxStreamsPerBlock * kMaxLevels : s * kMaxLevels + lev];
+    float total = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kCompareThreads / kWave; ++w) total += part[w];
+    if (!den)
+      a.num_part[(cell * a.n_streams + st0 + s) * a.n_levels + lev] = total;
+    else if (item.index == 0)
+      a.den_part[cell] = total;
   }
 }
 
@@ -774,7 +812,7 @@ extern "C" int32_t kvp_eval_configs_ex(const kvp_view* q_win, const kvp_view* k,
     a.ref_stream = a.n_streams++;
     a.streams[a.ref_stream] = StreamDesc{16, 128};
   }
-  // the reference stream walks the most tokens: give it the lowest block indices so that its blocks start first
+  // the reference is stream 0
   if (a.ref_stream != 0) {
     const StreamDesc first = a.streams[0];
     a.streams[0] = a.streams[a.ref_stream];
@@ -798,7 +836,7 @@ extern "C" int32_t kvp_eval_configs_ex(const kvp_view* q_win, const kvp_view* k,
   int32_t* idx = reinterpret_cast<int32_t*>(take(p.idx));
   a.shell = reinterpret_cast<uint8_t*>(take(p.shell));
   a.order = reinterpret_cast<int32_t*>(take(p.order));
-  a.o_levels = reinterpret_cast<float*>(take(p.o_levels));
+  a.o_parts = reinterpret_cast<float*>(take(p.o_levels));
   a.den_part = reinterpret_cast<float*>(take(p.den));
   a.num_part = reinterpret_cast<float*>(take(p.num));
   a.layer_part = reinterpret_cast<double*>(take(p.layer));
@@ -817,8 +855,12 @@ extern "C" int32_t kvp_eval_configs_ex(const kvp_view* q_win, const kvp_view* k,
   a.loss = loss;
   a.partial = partial;
 
-  const int64_t items = static_cast<int64_t>(p.RB) * p.LH * a.n_streams;
+  const int64_t cells = p.RB * p.LH, items = cells * a.n_streams;
   if (items >= (1ll << 30)) return KVP_ERR_SHAPE;   // before anything is enqueued
+  // The output region has room for n_levels + 1 slots of 64 KiB per stream and at least two streams.  One slot per level
+  // and one for the reference's extra segment are used, which leaves at least one per cell for the statistics (1 KiB each).
+  a.stats = reinterpret_cast<float2*>(a.o_parts + cells * (a.n_streams * a.n_levels + 1) * (kRowsPerBlock * kHeadDim));
+  const int64_t segments = cells * (a.n_streams * a.n_levels + (a.level_k[a.n_levels - 1] < T ? 1 : 0));   // < 2^23: 64 KiB each
   const hipStream_t st = as_stream(stream);
   rc = score_tokens_impl(q_win, k, 1, 1, scores, score_ws, p.score_ws, st);
   if (rc != KVP_OK) return rc;
@@ -832,16 +874,20 @@ extern "C" int32_t kvp_eval_configs_ex(const kvp_view* q_win, const kvp_view* k,
     }
   }
   build_order_kernel<<<dim3(static_cast<unsigned>(p.LH)), kOrderThreads, 0, st>>>(a);
-  const dim3 grid(static_cast<unsigned>(kXcds * ceil_div(items, kXcds)));
+  // streams per compare block: as many as leave a block for every CU, so that the reference is merged few times
+  const int spb = static_cast<int>(std::min<int64_t>(std::min(a.n_streams, kMaxStreamsPerBlock), std::max<int64_t>(1, items / 256)));
+  const dim3 grid(static_cast<unsigned>(kXcds * ceil_div(cells * ceil_div(a.n_streams, spb), kXcds)));
+  const size_t factors = (spb * a.n_levels + a.n_levels + 1) * kRowsPerBlock * sizeof(MergeFactors);
+  const dim3 seg_grid(static_cast<unsigned>(kXcds * ceil_div(segments, kXcds)));
   if (flags & KVP_EVAL_PV_MATRIX_CORES) {
-    attention_kernel<kPvMatrix><<<grid, kThreads, 0, st>>>(a);
-    compare_kernel<true><<<grid, kThreads, 0, st>>>(a);
+    attention_kernel<kPvMatrix><<<seg_grid, kThreads, 0, st>>>(a);
+    compare_kernel<true><<<grid, kCompareThreads, factors, st>>>(a, spb);
   } else if (flags & KVP_EVAL_PV_FP32) {
-    attention_kernel<kPvFp32><<<grid, kThreads, 0, st>>>(a);
-    compare_kernel<false><<<grid, kThreads, 0, st>>>(a);
+    attention_kernel<kPvFp32><<<seg_grid, kThreads, 0, st>>>(a);
+    compare_kernel<false><<<grid, kCompareThreads, factors, st>>>(a, spb);
   } else {
-    attention_kernel<kPvDot2><<<grid, kThreads, 0, st>>>(a);
-    compare_kernel<false><<<grid, kThreads, 0, st>>>(a);
+    attention_kernel<kPvDot2><<<seg_grid, kThreads, 0, st>>>(a);
+    compare_kernel<false><<<grid, kCompareThreads, factors, st>>>(a, spb);
   }
   finish_kernel<<<1, kFinishThreads, 0, st>>>(a);
   return launch_status();
