@@ -88,31 +88,32 @@ __device__ __forceinline__ int acc_row(int lane, int v) { return (lane >> 5) * 4
 // row is a chunk: block b's chunk of row lh keeps its statistics in this row of `partial` (b + lh grows with every chunk).
 __device__ __forceinline__ int64_t chunk_row(const ScoreArgs& a, uint32_t b, uint32_t lh) { return a.compact_rows ? b : b + lh; }
 
-// bias_r = max_r + log2(sum_r) over all key chunks of (layer, head) lh; +inf for padding rows (they then contribute 0).
-__device__ __forceinline__ float combined_bias(const ScoreArgs& a, int lh, int r) {
-  if (r >= a.M) return INFINITY;
-  const uint32_t b0 = __builtin_amdgcn_readfirstlane(a.div_block.quot(lh * a.units_lh));   // lh is uniform
-  const int n = __builtin_amdgcn_readfirstlane(a.div_block.quot((lh + 1) * a.units_lh - 1)) - b0 + 1;
-  const float2* part = a.partial + chunk_row(a, b0, lh) * a.Mrows + r;
+// max + log2(sum) over the statistics of n chunks (uniform), a row of them every Mrows.
+__device__ __forceinline__ float combined_chunks(const float2* part, int n, int Mrows) {
   constexpr int kAtOnce = 16;  // statistics requested at once (one memory latency instead of one per chunk)
   float m = -INFINITY, z = 0.0f;
   for (int c = 0; c < n; c += kAtOnce) {
     float2 p[kAtOnce];
 #pragma unroll
-    for (int i = 0; i < kAtOnce; ++i) p[i] = part[static_cast<int64_t>(min(c + i, n - 1)) * a.Mrows];
-#pragma unroll
-    for (int i = 0; i < kAtOnce; ++i)
-      if (c + i >= n) p[i] = make_float2(-INFINITY, 0.0f);
+    for (int i = 0; i < kAtOnce; ++i)   // n is uniform: no lane masks, and no loads beyond the last chunk
+      p[i] = c + i < n ? part[static_cast<int64_t>(c + i) * Mrows] : make_float2(-INFINITY, 0.0f);
     float m_new = m;
 #pragma unroll
     for (int i = 0; i < kAtOnce; ++i) m_new = fmaxf(m_new, p[i].x);
     if (m_new == -INFINITY) continue;
-    z *= __builtin_amdgcn_exp2f(m - m_new);   // references are integers: exact
+    z *= __builtin_amdgcn_exp2f(m - m_new);
 #pragma unroll
     for (int i = 0; i < kAtOnce; ++i) z += p[i].y * __builtin_amdgcn_exp2f(p[i].x - m_new);
     m = m_new;
   }
   return m + __builtin_amdgcn_logf(z);  // v_log_f32 is log2
+}
+// bias of row r of (layer, head) lh over all its key chunks; +inf for padding rows (they then contribute 0)
+__device__ __forceinline__ float combined_bias(const ScoreArgs& a, int lh, int r) {
+  if (r >= a.M) return INFINITY;
+  const uint32_t b0 = __builtin_amdgcn_readfirstlane(a.div_block.quot(lh * a.units_lh));   // lh is uniform
+  const int n = __builtin_amdgcn_readfirstlane(a.div_block.quot((lh + 1) * a.units_lh - 1)) - b0 + 1;
+  return combined_chunks(a.partial + chunk_row(a, b0, lh) * a.Mrows + r, n, a.Mrows);
 }
 
 template <int NQT, bool PASS_B>
@@ -578,7 +579,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_small_kernel(const ScoreArg
   for (int r = threadIdx.x; r < a.Mrows; r += kThreads) {
     wpos_s[r] = r % a.W;
     // rows beyond M carry +inf: they contribute 2^-inf = 0
-    if constexpr (PASS_B) bias_s[r] = a.fold_combine ? combined_bias(a, lh, r) : a.bias[static_cast<int64_t>(lh) * a.Mrows + r];
+    if constexpr (PASS_B) bias_s[r] = a.fold_combine ? (r < a.M ? combined_chunks(a.partial + static_cast<int64_t>(lh) * gridDim.x * a.Mrows + r, gridDim.x, a.Mrows) : INFINITY) : a.bias[static_cast<int64_t>(lh) * a.Mrows + r];
   }
   __syncthreads();
 
