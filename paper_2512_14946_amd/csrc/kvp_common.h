@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "kvp.h"
+#include "kvp_math.h"
 
 namespace kvp {
 
@@ -15,7 +16,6 @@ constexpr int kLanesPerRow = 16;       // 128 bf16 = 16 lanes x 16 bytes
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline int32_t launch_status() { return hipGetLastError() == hipSuccess ? KVP_OK : KVP_ERR_LAUNCH; }
-inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Division of a non-negative n < 2^31 by a divisor fixed at launch: multiply-high and shift.
 struct FastDiv {

@@ -40,6 +40,7 @@
 #include <type_traits>
 
 #include "kvp_internal.h"
+#include "score_plan.h"
 
 namespace kvp {
 namespace {
@@ -47,14 +48,10 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float floatx16;
 
-constexpr int kWaves = 8;                          // waves per block, two per SIMD (256 registers per wave)
+constexpr int kWaves = kScoreWaves;
 constexpr int kThreads = kWaves * kWave;
-constexpr int kUnitTiles = 2;                      // 32-key tiles a wave of a large call works on at a time
-constexpr int kSmallChunk = 32 * kWaves;           // keys per block of a small call
 constexpr int kPitch = 136;                        // bf16 elements per LDS row (272 B)
 constexpr int kMaxRows = 512;                      // G*W limit (16 query tiles)
-constexpr int kFoldChunks = 16;                    // up to this many key chunks per row pass B combines their statistics itself
-constexpr int kCUs = 256;                          // one block of 8 waves each
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct ScoreArgs {
@@ -776,52 +773,6 @@ __global__ void combine_kernel(const ScoreArgs a) {
   for (int r = threadIdx.x; r < a.Mrows; r += blockDim.x) a.bias[static_cast<int64_t>(lh) * a.Mrows + r] = combined_bias(a, lh, r);
 }
 
-// How the keys are shared out.  Large calls: 64-key units, 8 waves per block and one block per CU of the chip, every
-// block the same number of units, so that a block stages the queries of few (layer, head) rows (a chunk costs about 30 us
-// besides its keys at M = 512: staging, first loads, waves that wait for the last one; two or three blocks per CU measured
-// 2 and 4 % slower).  Small calls, less than one 64-key unit per wave of the chip: 256-key chunks, so that many CUs take
-// part (8 heads x 4096 keys, M = 128: 15 us for both passes, 20 us with the kernel of the large calls).
-struct ScorePlan {
-  int32_t M, nqt, Mrows;
-  bool wide, fold;
-  int64_t units_lh, units_block, units, blocks;
-  size_t partial_bytes, bytes;
-};
-
-// Scratch of a call.  The size is part of the interface (callers keep workspaces, and the 4 MiB of
-// kvp_score_tokens_static accept or refuse a shape by it), so it stays that of chunks of 256 .. 4096 keys, as few as fill
-// the chip twice, and a bias per row; no plan below needs more.
-size_t scratch_bytes(int64_t n_lh, int64_t T, int64_t Mrows) {
-  int64_t keys = 4096;
-  while (keys > 256 && n_lh * ceil_div(T, keys) < 512) keys /= 2;
-  const size_t partial = static_cast<size_t>(n_lh) * ceil_div(T, keys) * Mrows * sizeof(float2);
-  return (partial + 255) / 256 * 256 + static_cast<size_t>(n_lh) * Mrows * sizeof(float);
-}
-
-ScorePlan make_plan(int64_t L, int64_t Hkv, int64_t Hq, int64_t W, int64_t T) {
-  ScorePlan p{};
-  const int64_t n_lh = L * Hkv;
-  p.M = static_cast<int32_t>((Hq / Hkv) * W);
-  p.nqt = (p.M + 31) / 32;              // query tiles in use (1 .. 16)
-  p.Mrows = p.nqt * 32;
-  p.wide = n_lh * ceil_div(T, 32 * kUnitTiles) >= kCUs * kWaves;
-  if (p.wide) {
-    p.units_lh = ceil_div(T, 32 * kUnitTiles);
-    p.units_block = ceil_div(n_lh * p.units_lh, kCUs);
-  } else {
-    p.units_lh = ceil_div(T, kSmallChunk);
-    p.units_block = 1;
-  }
-  p.units = n_lh * p.units_lh;
-  p.blocks = ceil_div(p.units, p.units_block);
-  const int64_t chunks = p.wide ? p.blocks + n_lh - 1 : p.blocks;        // rows of `partial`
-  p.fold = (p.units_lh - 1) / p.units_block + (p.wide ? 2 : 1) <= kFoldChunks;      // chunks a (layer, head) row may have
-  p.partial_bytes = static_cast<size_t>(chunks) * p.Mrows * sizeof(float2);
-  p.partial_bytes = (p.partial_bytes + 255) / 256 * 256;
-  p.bytes = scratch_bytes(n_lh, T, p.Mrows);
-  return p;
-}
-
 // Instantiated for 1, 2, 4, 8 and 16 query tiles of LDS (M = 224 runs 7 tiles in the 8-tile instantiation); pass A of the
 // small calls for every tile count 1 .. 16 (its per-tile statistics live in registers with static indices).
 template <bool PASS_B>
@@ -863,7 +814,7 @@ int32_t score_tokens_impl(const kvp_view* q_win, const kvp_view* k, int32_t caus
   const int64_t L = k->L, T = k->T, Hkv = k->H, Hq = q_win->H, W = q_win->T;
   if (q_win->L != L || Hq % Hkv != 0 || W > T || T >= (1ll << 30) || L * Hkv > 65535) return KVP_ERR_SHAPE;
   if ((Hq / Hkv) * W > kMaxRows) return KVP_ERR_UNSUPPORTED;
-  const ScorePlan p = make_plan(L, Hkv, Hq, W, T);
+  const ScorePlan p = make_score_plan(L, Hkv, Hq, W, T);
   if (!ws || ws_bytes < p.bytes || (reinterpret_cast<uintptr_t>(ws) & 15u))
     return KVP_ERR_WORKSPACE;
 
@@ -908,7 +859,7 @@ int32_t score_tokens_impl(const kvp_view* q_win, const kvp_view* k, int32_t caus
 
 extern "C" size_t kvp_score_workspace_bytes(int64_t L, int64_t Hkv, int64_t Hq, int64_t W, int64_t T) {
   if (L <= 0 || Hkv <= 0 || Hq <= 0 || W <= 0 || T <= 0 || Hq % Hkv != 0) return 0;
-  const kvp::ScorePlan p = kvp::make_plan(L, Hkv, Hq, W, T);
+  const kvp::ScorePlan p = kvp::make_score_plan(L, Hkv, Hq, W, T);
   return p.bytes;
 }
 
