@@ -22,7 +22,7 @@
 // cover all 32 banks); keys go from global memory straight into MFMA operand registers.  Every key is owned by exactly one
 // wave and every sum is formed in a fixed order: deterministic output.
 //
-// What bounds it (large calls): the issue of matrix and vector instructions together, at the 1.9-2.0 GHz the chip holds
+// What bounds it (throughput kernel): the issue of matrix and vector instructions together, at the 1.9-2.0 GHz the chip holds
 // under this load.  A product of 32x32x16 takes 32 cycles of the matrix pipe; the six vector instructions that go with
 // it (two logits, two exponentials of 8 cycles, two sums) take 32 cycles, and 42 together measured in isolation with two
 // waves per SIMD; 65 in the kernel.  Hence (80 x 8 x 16384 keys, 512 rows: 3.17 -> 2.73 ms; 28 x 4 x 131072, 224 rows:
@@ -63,6 +63,7 @@ struct ScoreArgs {
   FastDiv div_w;                            // row r of the window queries: query head r / W, window offset r mod W
   uint32_t units_lh, units_block, units;    // key units per (layer, head), per block, in all
   FastDiv div_lh, div_block;                // by units_lh, by units_block
+  int32_t chunk_keys;                       // keys per block of the chunked kernel, a multiple of 32 * kWaves
   int32_t compact_rows;                     // blocks never span two (layer, head) rows: their statistics are numbered by block
   int32_t causal, force_window;
   int32_t fold_combine;                     // pass B combines the chunk statistics itself (few chunks: saves a launch)
@@ -103,7 +104,8 @@ __device__ __forceinline__ float combined_chunks(const float2* part, int n, int 
     for (int i = 0; i < kAtOnce; ++i) z += p[i].y * __builtin_amdgcn_exp2f(p[i].x - m_new);
     m = m_new;
   }
-  return m + __builtin_amdgcn_logf(z);  // v_log_f32 is log2
+  // v_log_f32 is log2; its error is smallest below 1
+  return m + static_cast<float>(__builtin_amdgcn_frexp_expf(z)) + __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(z));
 }
 // bias of row r of (layer, head) lh over all its key chunks; +inf for padding rows (they then contribute 0)
 __device__ __forceinline__ float combined_bias(const ScoreArgs& a, int lh, int r) {
@@ -513,10 +515,12 @@ __global__ __launch_bounds__(kThreads, 2) void score_kernel(const ScoreArgs a) {
   }
 }
 
-// ---- calls of few keys (256 per block, so that many CUs take part): latency counts, not throughput ----
+// ---- calls of few keys or of short rows: one chunk of one row per block, so that many blocks take part ----
 //
-// Each wave owns one 32-key tile, requested before the prologue, and walks the query tiles against it with two tiles in
-// flight; pass A in the textbook form (running maximum), which needs no prologue to find references.
+// Each wave owns every eighth 32-key tile of the chunk, the first one requested before the prologue and each further one
+// during the arithmetic of the one before, and walks the query tiles against it with two tiles in flight; pass A in the
+// textbook form, which needs no prologue to find references (the running maximum is rounded up to an integer, so that
+// rescaling is exact).
 // 32 keys starting at tk0 as an MFMA operand, straight from global memory: lane holds key
 // tk0 + lane%32, channels 16*ks + 8*(lane/32) .. +7.  Keys at or beyond T are zero.
 __device__ __forceinline__ void load_key_tile(const ScoreArgs& a, const uint16_t* kbase, int tk0, int lane, uint4 out[8]) {
@@ -532,7 +536,7 @@ __device__ __forceinline__ void load_key_tile(const ScoreArgs& a, const uint16_t
 }
 
 template <int NQT, bool PASS_B>
-__global__ __launch_bounds__(kThreads, 2) void score_small_kernel(const ScoreArgs a) {
+__global__ __launch_bounds__(kThreads, 2) void score_chunk_kernel(const ScoreArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t q_s[NQT * 32 * kPitch];
   __shared__ __attribute__((aligned(16))) float bias_s[PASS_B ? NQT * 32 : 4];
   __shared__ __attribute__((aligned(16))) int32_t wpos_s[NQT * 32];   // window offset r mod W of query row r (masked tiles)
@@ -547,8 +551,8 @@ __global__ __launch_bounds__(kThreads, 2) void score_small_kernel(const ScoreArg
 
   // this wave's first key tile is requested before anything else, so that its latency overlaps the prologue
   constexpr int kTileStride = 32 * kWaves;
-  const int t_begin = chunk * kSmallChunk + wave * 32;
-  const int t_end = min(a.T, (chunk + 1) * kSmallChunk);   // a multiple of kTileStride
+  const int t_begin = chunk * a.chunk_keys + wave * 32;
+  const int t_end = min(a.T, (chunk + 1) * a.chunk_keys);
   uint4 kop[8];
   if (t_begin < t_end) load_key_tile(a, kbase, t_begin, lane, kop);
 
@@ -623,7 +627,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_small_kernel(const ScoreArg
       float tmax = c[0];
 #pragma unroll
       for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, c[v]);
-      const float m_new = fmaxf(m_run, tmax * a.scale2);   // scale2 > 0: max commutes with it
+      const float m_new = fmaxf(m_run, __builtin_ceilf(tmax * a.scale2));   // scale2 > 0: max commutes with it
       const float m_safe = (m_new == -INFINITY) ? 0.0f : m_new;
       float z = z_run * __builtin_amdgcn_exp2f(m_run - m_safe);
 #pragma unroll
@@ -651,8 +655,10 @@ __global__ __launch_bounds__(kThreads, 2) void score_small_kernel(const ScoreArg
           }
         }
       }
+      float part = 0.0f;   // a sum of its own per tile: less rounding than adding every term to the column
 #pragma unroll
-      for (int v = 0; v < 16; ++v) col += __builtin_amdgcn_exp2f(fmaf(c[v], a.scale2, -bias[v]));
+      for (int v = 0; v < 16; ++v) part += __builtin_amdgcn_exp2f(fmaf(c[v], a.scale2, -bias[v]));
+      col += part;
     }
   };
 
@@ -774,7 +780,7 @@ __global__ void combine_kernel(const ScoreArgs a) {
 }
 
 // Instantiated for 1, 2, 4, 8 and 16 query tiles of LDS (M = 224 runs 7 tiles in the 8-tile instantiation); pass A of the
-// small calls for every tile count 1 .. 16 (its per-tile statistics live in registers with static indices).
+// chunked kernel for every tile count 1 .. 16 (its per-tile statistics live in registers with static indices).
 template <bool PASS_B>
 void launch_wide(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
   if (nqt <= 1) score_kernel<1, PASS_B><<<grid, kThreads, 0, st>>>(a);
@@ -785,19 +791,19 @@ void launch_wide(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
 }
 
 template <int N>
-void launch_small_a(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
+void launch_chunked_a(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
   if constexpr (N <= 16) {
-    if (nqt == N) score_small_kernel<N, false><<<grid, kThreads, 0, st>>>(a);
-    else launch_small_a<N + 1>(nqt, grid, st, a);
+    if (nqt == N) score_chunk_kernel<N, false><<<grid, kThreads, 0, st>>>(a);
+    else launch_chunked_a<N + 1>(nqt, grid, st, a);
   }
 }
 
-void launch_small_b(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
-  if (nqt <= 1) score_small_kernel<1, true><<<grid, kThreads, 0, st>>>(a);
-  else if (nqt <= 2) score_small_kernel<2, true><<<grid, kThreads, 0, st>>>(a);
-  else if (nqt <= 4) score_small_kernel<4, true><<<grid, kThreads, 0, st>>>(a);
-  else if (nqt <= 8) score_small_kernel<8, true><<<grid, kThreads, 0, st>>>(a);
-  else score_small_kernel<16, true><<<grid, kThreads, 0, st>>>(a);
+void launch_chunked_b(int nqt, dim3 grid, hipStream_t st, const ScoreArgs& a) {
+  if (nqt <= 1) score_chunk_kernel<1, true><<<grid, kThreads, 0, st>>>(a);
+  else if (nqt <= 2) score_chunk_kernel<2, true><<<grid, kThreads, 0, st>>>(a);
+  else if (nqt <= 4) score_chunk_kernel<4, true><<<grid, kThreads, 0, st>>>(a);
+  else if (nqt <= 8) score_chunk_kernel<8, true><<<grid, kThreads, 0, st>>>(a);
+  else score_chunk_kernel<16, true><<<grid, kThreads, 0, st>>>(a);
 }
 
 }  // namespace
@@ -830,6 +836,7 @@ int32_t score_tokens_impl(const kvp_view* q_win, const kvp_view* k, int32_t caus
   a.units_lh = static_cast<uint32_t>(p.units_lh); a.units_block = static_cast<uint32_t>(p.units_block);
   a.units = static_cast<uint32_t>(p.units);
   a.div_lh = FastDiv(a.units_lh); a.div_block = FastDiv(a.units_block);
+  a.chunk_keys = p.chunk_keys;
   a.compact_rows = p.wide ? 0 : 1;
   a.causal = causal ? 1 : 0; a.force_window = force_window ? 1 : 0;
   a.scale2 = kLog2e / sqrtf(static_cast<float>(kHeadDim));
@@ -848,9 +855,9 @@ int32_t score_tokens_impl(const kvp_view* q_win, const kvp_view* k, int32_t caus
     launch_wide<true>(p.nqt, grid, st, a);
   } else {
     const dim3 grid(static_cast<unsigned>(p.units_lh), rows.x);
-    launch_small_a<1>(p.nqt, grid, st, a);
+    launch_chunked_a<1>(p.nqt, grid, st, a);
     if (!p.fold) combine_kernel<<<rows, 256, 0, st>>>(a);
-    launch_small_b(p.nqt, grid, st, a);
+    launch_chunked_b(p.nqt, grid, st, a);
   }
   return launch_status();
 }

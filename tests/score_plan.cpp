@@ -1,6 +1,7 @@
 // Checks the sharing-out of kvp_score_tokens over its range: every key unit belongs to one chunk, every chunk has a row of
 // statistics of its own inside the scratch memory, a row combined in the prologue has at most kFoldChunks chunks, and the
-// scratch size stays the one callers know.  Prints the number of plans walked and of sizes checked.
+// scratch size stays the one callers know.  Prints the number of plans walked and of sizes checked; with a shape as arguments,
+// which kernel runs it.
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -57,7 +58,13 @@ static void walk(int64_t n_lh, int64_t M, int64_t T) {
   }
 }
 
-int main() {
+int main(int argc, char** argv) {
+  if (argc == 6) {   // L Hkv Hq W T: 1 when the call runs the throughput kernel
+    int64_t v[5];
+    for (int i = 0; i < 5; ++i) v[i] = atoll(argv[i + 1]);
+    printf("%d\n", make_score_plan(v[0], v[1], v[2], v[3], v[4]).wide ? 1 : 0);
+    return 0;
+  }
   const int64_t edges[] = {1,   31,  32,   33,   63,   64,   65,   127,  128,  129,  192,  193,   255,   256,   257,    300,   448,
                            511, 512, 513, 700, 1000, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097, 5000, 8192, 16384, 16385,
                            32768, 65536, 131072, 131073};
@@ -75,7 +82,7 @@ int main() {
       if (n * T <= (int64_t)1 << 24) { walk(n, 512, T); ++walks; }
   for (int i = 0; i < 2000; ++i) {
     const int64_t n = log_int(0, 13);
-    walk(n, 64, log_int(0, 22 - log2((double)n)));
+    walk(n, 1 + (int64_t)(rng() % 512), log_int(0, 23 - log2((double)n)));
     ++walks;
   }
   printf("%ld %ld\n", walks, sizes);
