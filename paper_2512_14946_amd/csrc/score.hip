@@ -87,32 +87,36 @@ __device__ __forceinline__ int acc_row(int lane, int v) { return (lane >> 5) * 4
 __device__ __forceinline__ int64_t chunk_row(const ScoreArgs& a, uint32_t b, uint32_t lh) { return a.compact_rows ? b : b + lh; }
 
 // max + log2(sum) over the statistics of n chunks (uniform), a row of them every Mrows.
+// FEW: n is at most kFoldChunks, the statistics in flight at once (one memory latency instead of one per chunk).
+template <bool FEW>
 __device__ __forceinline__ float combined_chunks(const float2* part, int n, int Mrows) {
-  constexpr int kAtOnce = 16;  // statistics requested at once (one memory latency instead of one per chunk)
   float m = -INFINITY, z = 0.0f;
-  for (int c = 0; c < n; c += kAtOnce) {
-    float2 p[kAtOnce];
+  for (int c = 0; c < (FEW ? 1 : n); c += kFoldChunks) {
+    float2 p[kFoldChunks];
 #pragma unroll
-    for (int i = 0; i < kAtOnce; ++i)   // n is uniform: no lane masks, and no loads beyond the last chunk
+    for (int i = 0; i < kFoldChunks; ++i)   // n is uniform: no lane masks, and no loads beyond the last chunk
       p[i] = c + i < n ? part[static_cast<int64_t>(c + i) * Mrows] : make_float2(-INFINITY, 0.0f);
     float m_new = m;
 #pragma unroll
-    for (int i = 0; i < kAtOnce; ++i) m_new = fmaxf(m_new, p[i].x);
-    if (m_new == -INFINITY) continue;
-    z *= __builtin_amdgcn_exp2f(m - m_new);
+    for (int i = 0; i < kFoldChunks; ++i) m_new = fmaxf(m_new, p[i].x);
+    if (!FEW) {
+      if (m_new == -INFINITY) continue;
+      z *= __builtin_amdgcn_exp2f(m - m_new);
+    }
 #pragma unroll
-    for (int i = 0; i < kAtOnce; ++i) z += p[i].y * __builtin_amdgcn_exp2f(p[i].x - m_new);
+    for (int i = 0; i < kFoldChunks; ++i) z += p[i].y * __builtin_amdgcn_exp2f(p[i].x - m_new);
     m = m_new;
   }
   // v_log_f32 is log2; its error is smallest below 1
   return m + static_cast<float>(__builtin_amdgcn_frexp_expf(z)) + __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(z));
 }
 // bias of row r of (layer, head) lh over all its key chunks; +inf for padding rows (they then contribute 0)
+template <bool FEW>
 __device__ __forceinline__ float combined_bias(const ScoreArgs& a, int lh, int r) {
   if (r >= a.M) return INFINITY;
   const uint32_t b0 = __builtin_amdgcn_readfirstlane(a.div_block.quot(lh * a.units_lh));   // lh is uniform
   const int n = __builtin_amdgcn_readfirstlane(a.div_block.quot((lh + 1) * a.units_lh - 1)) - b0 + 1;
-  return combined_chunks(a.partial + chunk_row(a, b0, lh) * a.Mrows + r, n, a.Mrows);
+  return combined_chunks<FEW>(a.partial + chunk_row(a, b0, lh) * a.Mrows + r, n, a.Mrows);
 }
 
 template <int NQT, bool PASS_B>
@@ -182,7 +186,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_kernel(const ScoreArgs a) {
   for (int r = threadIdx.x; r < a.Mrows; r += kThreads) {
     wpos_s[r] = r - static_cast<int>(a.div_w.quot(r)) * a.W;
     // rows beyond M carry +inf: they contribute 2^-inf = 0
-    if constexpr (PASS_B) row_s[r] = a.fold_combine ? combined_bias(a, lh, r) : a.bias[static_cast<int64_t>(lh) * a.Mrows + r];
+    if constexpr (PASS_B) row_s[r] = a.fold_combine ? combined_bias<true>(a, lh, r) : a.bias[static_cast<int64_t>(lh) * a.Mrows + r];
   }
   if (PASS_B && threadIdx.x == 0) ticket_s = 2 * kWaves;
   if constexpr (!PASS_B) {
@@ -580,7 +584,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_chunk_kernel(const ScoreArg
   for (int r = threadIdx.x; r < a.Mrows; r += kThreads) {
     wpos_s[r] = r % a.W;
     // rows beyond M carry +inf: they contribute 2^-inf = 0
-    if constexpr (PASS_B) bias_s[r] = a.fold_combine ? (r < a.M ? combined_chunks(a.partial + static_cast<int64_t>(lh) * gridDim.x * a.Mrows + r, gridDim.x, a.Mrows) : INFINITY) : a.bias[static_cast<int64_t>(lh) * a.Mrows + r];
+    if constexpr (PASS_B) bias_s[r] = a.fold_combine ? (r < a.M ? combined_chunks<true>(a.partial + static_cast<int64_t>(lh) * gridDim.x * a.Mrows + r, gridDim.x, a.Mrows) : INFINITY) : a.bias[static_cast<int64_t>(lh) * a.Mrows + r];
   }
   __syncthreads();
 
@@ -776,7 +780,7 @@ __global__ __launch_bounds__(kThreads, 2) void score_chunk_kernel(const ScoreArg
 // The same combination as its own launch, once per (layer, head), when there are many chunks.
 __global__ void combine_kernel(const ScoreArgs a) {
   const int lh = blockIdx.x;
-  for (int r = threadIdx.x; r < a.Mrows; r += blockDim.x) a.bias[static_cast<int64_t>(lh) * a.Mrows + r] = combined_bias(a, lh, r);
+  for (int r = threadIdx.x; r < a.Mrows; r += blockDim.x) a.bias[static_cast<int64_t>(lh) * a.Mrows + r] = combined_bias<false>(a, lh, r);
 }
 
 // Instantiated for 1, 2, 4, 8 and 16 query tiles of LDS (M = 224 runs 7 tiles in the 8-tile instantiation); pass A of the
