@@ -586,6 +586,9 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
 constexpr int kCompareThreads = 1024;
 constexpr int kMaxStreamsPerBlock = 5;
 struct MergeFactors { float keep, add, inv; };
+// merge factors and partial sums of the largest block (78 KB) fit a CU's 160 KB; the runtime takes them without an opt-in
+static_assert(((kMaxStreamsPerBlock + 1) * kMaxLevels + 1) * kRowsPerBlock * sizeof(MergeFactors) +
+                  (kMaxStreamsPerBlock * kMaxLevels + 1) * (kCompareThreads / kWave) * sizeof(float) <= 160 * 1024, "LDS of a compare block");
 template <bool PV_MFMA>
 __global__ __launch_bounds__(kCompareThreads, 4) void compare_kernel(const EvalArgs a, int spb) {
   extern __shared__ MergeFactors factors_s[];   // [spb * n_levels (streams) + n_ref (reference)][128 rows]
