@@ -42,7 +42,9 @@
 //     per-query rescaling is lane-private.
 
 #include <algorithm>
+#include <type_traits>
 
+#include "eval_plan.h"
 #include "kvp_internal.h"
 #include "quant_device.h"
 
@@ -65,7 +67,7 @@ constexpr int kTile = 32;                  // tokens per tile
 constexpr int kRowsPerBlock = 128;         // query rows per block
 constexpr int kPitch = 136;                // bf16 elements per staged K row (272 B)
 constexpr int kMaxCfgs = 64;
-constexpr int kMaxLevels = 8;
+constexpr int kMaxLevels = kEvalMaxLevels;
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct StreamDesc {
@@ -86,6 +88,8 @@ struct EvalArgs {
   const int32_t* level_idx[kMaxLevels];  // [L*Hkv][k] ascending keep list, or null when k == T
   StreamDesc streams[kMaxCfgs + 1];      // + a hidden 16-bit stream when no configuration asks for one
   int32_t ref_stream;                    // the 16-bit stream: it walks all T tokens and is the reference
+  int32_t walk, grouped;                 // which blocks attention_kernel has, see choose_blocks
+  uint8_t seg_rank[kMaxLevels + 1];
   uint8_t cfg_stream[kMaxCfgs], cfg_level[kMaxCfgs];
   uint8_t* shell;   // [L*Hkv][T] scratch: index of the first keep level that holds the token
   int32_t* order;   // [L*Hkv][T] tokens ordered by shell, ascending inside a shell
@@ -261,13 +265,14 @@ struct WorkItem {
   int rb, lh, index;
   bool valid;
 };
-constexpr int kXcds = 8;
-__device__ __forceinline__ WorkItem work_item(const EvalArgs& a, int per_cell) {
+constexpr int kXcds = kEvalXcds;
+__device__ __forceinline__ int items_per_xcd(int items) { return (items + kXcds - 1) / kXcds; }
+__device__ __forceinline__ WorkItem work_item(const EvalArgs& a, int per_cell, int block) {
   const int items = a.RB * a.L * a.Hkv * per_cell;
-  const int per_xcd = (items + kXcds - 1) / kXcds;
-  const int w = static_cast<int>(blockIdx.x % kXcds) * per_xcd + static_cast<int>(blockIdx.x / kXcds);
+  const int per_xcd = items_per_xcd(items);
+  const int w = block % kXcds * per_xcd + block / kXcds;
   WorkItem it;
-  it.valid = static_cast<int>(blockIdx.x / kXcds) < per_xcd && w < items;
+  it.valid = block / kXcds < per_xcd && w < items;
   it.index = w % per_cell;
   const int cell = w / per_cell;
   it.rb = cell % a.RB;
@@ -275,9 +280,8 @@ __device__ __forceinline__ WorkItem work_item(const EvalArgs& a, int per_cell) {
   return it;
 }
 
-// One launch covers every segment of every stream, a block for each: a context of 8 layers x 4 kv heads (224 rows, ten
-// streams) is 640 blocks with whole streams, one and a quarter times what the chip holds at once, and 2560 with segments
-// (measured with matrix-core P.V: 0.92 -> 0.71 ms).  The outputs are combined and compared afterwards (compare_kernel).
+// One launch covers every segment of every stream; the outputs are combined and compared afterwards (compare_kernel).
+// Which blocks there are: choose_blocks.
 // PV: how the P.V product is formed (kPvDot2: packed fp16 pairs on the vector ALU; kPvMatrix: two-term bf16 split
 // of P on the matrix cores; kPvFp32: fp32 on the vector ALU).
 template <int PV>
@@ -300,13 +304,29 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5;
+  // This block's work item and its segments [seg0, n_seg) (see choose_blocks).
   const int extra = extra_segment(a) ? 1 : 0;
-  const WorkItem item = work_item(a, a.n_streams * a.n_levels + extra);
+  int block = blockIdx.x, per_cell = a.walk ? a.n_streams : a.n_streams * a.n_levels + extra, seg0 = 0;
+  if (a.grouped) {   // by segment, in the order of seg_rank; the streams of a cell side by side
+    for (int i = 0;; ++i) {
+      seg0 = a.seg_rank[i];
+      per_cell = seg0 == a.n_levels ? 1 : a.n_streams;
+      const int blocks = items_per_xcd(a.RB * a.L * a.Hkv * per_cell) * kXcds;
+      if (block < blocks) break;
+      block -= blocks;
+    }
+  }
+  const WorkItem item = work_item(a, per_cell, block);
   if (!item.valid) return;
   const int rb = item.rb, lh = item.lh;
-  // the segment nobody keeps may be the longest: first
-  const int stream = item.index < extra ? a.ref_stream : (item.index - extra) % a.n_streams;
-  const int seg = item.index < extra ? a.n_levels : (item.index - extra) / a.n_streams;
+  int stream = item.index;
+  if (a.grouped) {
+    if (seg0 == a.n_levels) stream = a.ref_stream;
+  } else if (!a.walk) {   // by cell; the segment nobody keeps may be the longest: first
+    stream = item.index < extra ? a.ref_stream : (item.index - extra) % a.n_streams;
+    seg0 = item.index < extra ? a.n_levels : (item.index - extra) / a.n_streams;
+  }
+  const int n_seg = !a.walk ? seg0 + 1 : a.n_levels + (stream == a.ref_stream ? extra : 0);
   const int l = lh / a.Hkv, h = lh - l * a.Hkv;
   const int bits = a.streams[stream].bits, group = a.streams[stream].group;
   const int32_t* order = a.order + static_cast<int64_t>(lh) * a.T;
@@ -335,19 +355,35 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
   // Output accumulators, 64 per thread.
   //   matrix cores: O^T of this wave's 32 queries, o[16 ct + v] = channel 32 ct + acc_row(lane, v) of query lane%32
   //   vector ALU:   an 8x8 tile, o[8 i + j] = row prow + i (of this wave's 32), channel {4tx.., 64+4tx..}[j]
+  // A product whose three operands lie in one of the four register banks (number mod 4) is a cycle late.  The accumulators
+  // of the vector forms are declared in reverse and the stores' indices are formed anew, so that the compiler's allotment has
+  // 4 such products of 256 (fp32; 5 in the default form); in order and with indices kept through the loop it has 13 and 23,
+  // and a sweep context takes 10.27 instead of 10.01 ms in fp32.
+  auto slot = [](int e) { return PV_MFMA ? e : 63 - e; };
   float o[64];
 #pragma unroll
   for (int i = 0; i < 64; ++i) o[i] = 0.0f;
   const int tx = lane & 15, prow = wave * 32 + 8 * (lane >> 4);
-  const int seg_begin = seg > 0 ? a.level_k[seg - 1] : 0, seg_end = seg < a.n_levels ? a.level_k[seg] : a.T;
-
-  // Tile = positions [pos, min(pos + 32, seg_end)) of the token order.  Global loads run ahead of the arithmetic: the
-  // permutation entries of a tile are fetched two tiles early and its K and V rows one tile early, so neither of the two
-  // dependent latencies sits between two tiles.
+  // Tile cursor: tile = positions [pos, min(pos + 32, end)) of segment seg.  Global loads run ahead of the arithmetic, across
+  // segments: the permutation entries of a tile are fetched two tiles early and its K and V rows one tile early, so neither
+  // of the two dependent latencies sits between two tiles.
+  auto seg_end_of = [&](int sg) { return sg < a.n_levels ? a.level_k[sg] : a.T; };
+  struct Cursor { int pos, seg, end; };
+  constexpr bool kCursor = PV != kPvFp32;   // the loop can go on into the next segment; the fp32 form's is faster without
+  auto in_range = [&](const Cursor& c) { return kCursor ? c.seg < n_seg : c.pos < c.end; };
+  auto advance = [&](Cursor c) {
+    c.pos += kTile;
+    if (kCursor && c.pos >= c.end && c.seg < n_seg) {
+      c.pos = c.end;
+      c.seg += 1;
+      if (c.seg < n_seg) c.end = seg_end_of(c.seg);
+    }
+    return c;
+  };
   const int tk_a = tid >> 4, tk_b = (tid + kThreads) >> 4, part = tid & 15;   // this thread's two staging slots
-  auto load_token = [&](int pos, int tk) {
+  auto load_token = [&](const Cursor& c, int tk) {
     int t = 0x7fffffff;  // beyond every query position: masked
-    if (pos + tk < seg_end) t = min(max(order[pos + tk], 0), a.T - 1);
+    if ((!kCursor || c.seg < n_seg) && c.pos + tk < c.end) t = min(max(order[c.pos + tk], 0), a.T - 1);
     return t;
   };
   auto load_row = [&](const uint16_t* base, int64_t stride, int t) {
@@ -382,14 +418,17 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
     has_window |= (t >= win0);   // window tokens and padding slots of a ragged tile need the mask
   };
 
-  int t_a = load_token(seg_begin, tk_a), t_b = load_token(seg_begin, tk_b);
+  Cursor cur{seg0 > 0 ? a.level_k[seg0 - 1] : 0, seg0, seg_end_of(seg0)};
+  Cursor nxt = advance(cur);
+  int t_a = load_token(cur, tk_a), t_b = load_token(cur, tk_b);
   uint4 k_a = load_row(kbase, a.k_st, t_a), v_a = load_row(vbase, a.v_st, t_a);
   uint4 k_b = load_row(kbase, a.k_st, t_b), v_b = load_row(vbase, a.v_st, t_b);
-  int tn_a = load_token(seg_begin + kTile, tk_a), tn_b = load_token(seg_begin + kTile, tk_b);
+  int tn_a = load_token(nxt, tk_a), tn_b = load_token(nxt, tk_b);
 
   if (tid == 0) mask_s[0] = mask_s[1] = 0;
   int parity = 0;
-  for (int pos = seg_begin; pos < seg_end; pos += kTile) {
+  while (in_range(cur)) {
+    const int seg = cur.seg;
     {
       __syncthreads();  // the previous tile's LDS is no longer read
       if (tid == 0) mask_s[parity ^ 1] = 0;   // the previous tile's flag has been read by everybody
@@ -399,14 +438,17 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
       stage(tk_b, t_b, k_b, v_b);
       if (has_window) mask_s[parity] = 1;     // rare; every writer stores the same value
       // ---- run ahead: rows of the next tile, permutation entries of the one after ----
+      const Cursor nn = advance(nxt);
       t_a = tn_a;
       t_b = tn_b;
       k_a = load_row(kbase, a.k_st, t_a);
       v_a = load_row(vbase, a.v_st, t_a);
       k_b = load_row(kbase, a.k_st, t_b);
       v_b = load_row(vbase, a.v_st, t_b);
-      tn_a = load_token(pos + 2 * kTile, tk_a);
-      tn_b = load_token(pos + 2 * kTile, tk_b);
+      tn_a = load_token(nn, tk_a);
+      tn_b = load_token(nn, tk_b);
+      cur = nxt;
+      nxt = nn;
       __syncthreads();                         // publishes the stage and the flag
       const bool need_mask = mask_s[parity] != 0;
       parity ^= 1;
@@ -514,7 +556,7 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
 #pragma unroll
           for (int i = 0; i < 8; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) o[8 * i + j] *= al[i];
+            for (int j = 0; j < 8; ++j) o[slot(8 * i + j)] *= al[i];
         }
         if constexpr (PV_DOT2) {
 #pragma unroll 4
@@ -529,7 +571,7 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
             for (int i = 0; i < 8; ++i)
 #pragma unroll
               for (int j = 0; j < 8; ++j)
-                o[8 * i + j] = __builtin_amdgcn_fdot2(as_half2(pr[i]), as_half2(vc[j]), o[8 * i + j], false);
+                o[slot(8 * i + j)] = __builtin_amdgcn_fdot2(as_half2(pr[i]), as_half2(vc[j]), o[slot(8 * i + j)], false);
           }
         } else {
 #pragma unroll 4
@@ -543,36 +585,41 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
 #pragma unroll
             for (int i = 0; i < 8; ++i)
 #pragma unroll
-              for (int j = 0; j < 8; ++j) o[8 * i + j] = fmaf(pr[i], vc[j], o[8 * i + j]);
+              for (int j = 0; j < 8; ++j) o[slot(8 * i + j)] = fmaf(pr[i], vc[j], o[slot(8 * i + j)]);
           }
         }
       }
     }
-  }
+    if (kCursor ? cur.seg == seg : in_range(cur)) continue;   // more tiles in this segment
 
-  // ---- the normalized output of this segment and its statistics; a row that sees none of its tokens has sum 0 ----
-  const int64_t cell = static_cast<int64_t>(lh) * a.RB + rb;
-  const float z = run_z + __shfl_xor(run_z, 32, 64);
-  if (lane < 32) stats_of(a, cell, stream, seg)[wave * 32 + lane] = make_float2(run_m, z);
-  float inv[8];      // 1 / row sum of the rows this thread's accumulators belong to
-  if constexpr (PV_MFMA) {
+    // ---- end of a segment: the normalized output of what this block has seen so far, and its statistics (one segment per
+    //      block; a row that sees none of its tokens has sum 0) ----
+    int tid2 = threadIdx.x;
+    asm volatile("" : "+v"(tid2));   // not known to be tid
+    const int lane2 = tid2 & 63, wave2 = tid2 >> 6;
+    const int64_t cell = static_cast<int64_t>(lh) * a.RB + rb;
+    const float z = run_z + __shfl_xor(run_z, 32, 64);
+    if (!a.walk && lane2 < 32) stats_of(a, cell, stream, seg)[wave2 * 32 + lane2] = make_float2(run_m, z);
+    float inv[8];      // 1 / row sum of the rows this thread's accumulators belong to
+    if constexpr (PV_MFMA) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) inv[i] = z == 0.0f ? 0.0f : 1.0f / z;
-  } else {
-    if (lane < 32) z_s[wave * 32 + lane] = z == 0.0f ? 0.0f : 1.0f / z;
-    __syncthreads();
+      for (int i = 0; i < 8; ++i) inv[i] = z == 0.0f ? 0.0f : 1.0f / z;
+    } else {
+      if (lane2 < 32) z_s[wave2 * 32 + lane2] = z == 0.0f ? 0.0f : 1.0f / z;
+      __syncthreads();
 #pragma unroll
-    for (int i = 0; i < 8; ++i) inv[i] = z_s[prow + i];
-  }
-  // each thread's 64 values are contiguous
-  float4* out = reinterpret_cast<float4*>(a.o_parts + out_slot(a, cell, stream, seg) * (kRowsPerBlock * kHeadDim) + tid * 64);
-#pragma unroll
-  for (int i = 0; i < 8; ++i)       // accumulators 8 i .. 8 i + 7 share a row in the vector-ALU layout
-#pragma unroll
-    for (int jh = 0; jh < 2; ++jh) {
-      const int e = 8 * i + 4 * jh;
-      out[e >> 2] = make_float4(o[e] * inv[i], o[e + 1] * inv[i], o[e + 2] * inv[i], o[e + 3] * inv[i]);
+      for (int i = 0; i < 8; ++i) inv[i] = z_s[wave2 * 32 + 8 * (lane2 >> 4) + i];
     }
+    // each thread's 64 values are contiguous
+    float4* out = reinterpret_cast<float4*>(a.o_parts + out_slot(a, cell, stream, seg) * (kRowsPerBlock * kHeadDim) + tid2 * 64);
+#pragma unroll
+    for (int i = 0; i < 8; ++i)       // accumulators 8 i .. 8 i + 7 share a row in the vector-ALU layout
+#pragma unroll
+      for (int jh = 0; jh < 2; ++jh) {
+        const int e = 8 * i + 4 * jh;
+        out[e >> 2] = make_float4(o[slot(e)] * inv[i], o[slot(e + 1)] * inv[i], o[slot(e + 2)] * inv[i], o[slot(e + 3)] * inv[i]);
+      }
+  }
 }
 
 // Squared distances between every level of every stream and the reference, and the reference's own squared norm; one
@@ -595,7 +642,7 @@ __global__ __launch_bounds__(kCompareThreads, 4) void compare_kernel(const EvalA
   __shared__ float red_s[kMaxStreamsPerBlock * kMaxLevels + 1][kCompareThreads / kWave];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n_groups = (a.n_streams + spb - 1) / spb;
-  const WorkItem item = work_item(a, n_groups);
+  const WorkItem item = work_item(a, n_groups, blockIdx.x);
   if (!item.valid) return;
   const int rb = item.rb;
   const int64_t cell = static_cast<int64_t>(item.lh) * a.RB + rb;
@@ -603,7 +650,7 @@ __global__ __launch_bounds__(kCompareThreads, 4) void compare_kernel(const EvalA
   const int64_t per_slot = kRowsPerBlock * kHeadDim;
   const int n_ref = a.n_levels + (extra_segment(a) ? 1 : 0);
   MergeFactors* ref_s = factors_s + spb * a.n_levels * kRowsPerBlock;
-  for (int i = tid; i < (n_st + 1) * kRowsPerBlock; i += kCompareThreads) {
+  for (int i = tid; i < (n_st + 1) * kRowsPerBlock && !a.walk; i += kCompareThreads) {
     const int row = i & (kRowsPerBlock - 1), s = i / kRowsPerBlock;   // s == n_st: the reference
     const int n = s == n_st ? n_ref : a.n_levels, st = s == n_st ? a.ref_stream : st0 + s;
     MergeFactors* out = (s == n_st ? ref_s : factors_s + s * a.n_levels * kRowsPerBlock) + row;
@@ -617,6 +664,8 @@ __global__ __launch_bounds__(kCompareThreads, 4) void compare_kernel(const EvalA
       out[sg * kRowsPerBlock] = MergeFactors{keep, add, 1.0f / z};
     }
   }
+  if (a.walk)   // every stored output is that of its level: nothing to merge
+    for (int i = tid; i < (spb * a.n_levels + n_ref) * kRowsPerBlock; i += kCompareThreads) factors_s[i] = MergeFactors{0.0f, 1.0f, 1.0f};
   __syncthreads();
   // piece f = 1024 j + tid is piece (f mod 16) of the run of writer thread f / 16
   constexpr int kPieces = kRowsPerBlock * kHeadDim / 4 / kCompareThreads;
@@ -641,7 +690,7 @@ __global__ __launch_bounds__(kCompareThreads, 4) void compare_kernel(const EvalA
   };
 #pragma unroll
   for (int j = 0; j < kPieces; ++j) r[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  for (int sg = 0; sg < n_ref; ++sg) {
+  for (int sg = a.walk ? n_ref - 1 : 0; sg < n_ref; ++sg) {
     const float4* val = reinterpret_cast<const float4*>(a.o_parts + out_slot(a, cell, a.ref_stream, sg) * per_slot);
 #pragma unroll
     for (int j = 0; j < kPieces; ++j) merge(r[j], val[kCompareThreads * j + tid], ref_s[sg * kRowsPerBlock + row[j]]);
@@ -863,7 +912,11 @@ extern "C" int32_t kvp_eval_configs_ex(const kvp_view* q_win, const kvp_view* k,
   // The output region has room for n_levels + 1 slots of 64 KiB per stream and at least two streams.  One slot per level
   // and one for the reference's extra segment are used, which leaves at least one per cell for the statistics (1 KiB each).
   a.stats = reinterpret_cast<float2*>(a.o_parts + cells * (a.n_streams * a.n_levels + 1) * (kRowsPerBlock * kHeadDim));
-  const int64_t segments = cells * (a.n_streams * a.n_levels + (a.level_k[a.n_levels - 1] < T ? 1 : 0));   // < 2^23: 64 KiB each
+  // fewer than 2^23 blocks: each of their segments takes 64 KiB of the workspace
+  const EvalBlocks plan = choose_blocks(cells, a.n_streams, a.n_levels, a.level_k, a.T, (flags & KVP_EVAL_PV_MATRIX_CORES) != 0);
+  a.walk = plan.walk;
+  a.grouped = plan.grouped;
+  std::copy(plan.seg_rank, plan.seg_rank + kMaxLevels + 1, a.seg_rank);
   const hipStream_t st = as_stream(stream);
   rc = score_tokens_impl(q_win, k, 1, 1, scores, score_ws, p.score_ws, st);
   if (rc != KVP_OK) return rc;
@@ -881,17 +934,15 @@ extern "C" int32_t kvp_eval_configs_ex(const kvp_view* q_win, const kvp_view* k,
   const int spb = static_cast<int>(std::min<int64_t>(std::min(a.n_streams, kMaxStreamsPerBlock), std::max<int64_t>(1, items / 256)));
   const dim3 grid(static_cast<unsigned>(kXcds * ceil_div(cells * ceil_div(a.n_streams, spb), kXcds)));
   const size_t factors = (spb * a.n_levels + a.n_levels + 1) * kRowsPerBlock * sizeof(MergeFactors);
-  const dim3 seg_grid(static_cast<unsigned>(kXcds * ceil_div(segments, kXcds)));
-  if (flags & KVP_EVAL_PV_MATRIX_CORES) {
-    attention_kernel<kPvMatrix><<<seg_grid, kThreads, 0, st>>>(a);
-    compare_kernel<true><<<grid, kCompareThreads, factors, st>>>(a, spb);
-  } else if (flags & KVP_EVAL_PV_FP32) {
-    attention_kernel<kPvFp32><<<seg_grid, kThreads, 0, st>>>(a);
-    compare_kernel<false><<<grid, kCompareThreads, factors, st>>>(a, spb);
-  } else {
-    attention_kernel<kPvDot2><<<seg_grid, kThreads, 0, st>>>(a);
-    compare_kernel<false><<<grid, kCompareThreads, factors, st>>>(a, spb);
-  }
+  const dim3 att_grid(static_cast<unsigned>(plan.blocks));
+  auto attend = [&](auto pv) {
+    constexpr int PV = decltype(pv)::value;
+    attention_kernel<PV><<<att_grid, kThreads, 0, st>>>(a);
+    compare_kernel<PV == kPvMatrix><<<grid, kCompareThreads, factors, st>>>(a, spb);
+  };
+  if (flags & KVP_EVAL_PV_MATRIX_CORES) attend(std::integral_constant<int, kPvMatrix>{});
+  else if (flags & KVP_EVAL_PV_FP32) attend(std::integral_constant<int, kPvFp32>{});
+  else attend(std::integral_constant<int, kPvDot2>{});
   finish_kernel<<<1, kFinishThreads, 0, st>>>(a);
   return launch_status();
 }

@@ -1,5 +1,6 @@
 """GPU parity of kvp_eval_configs where its comparison step takes several streams per block: short contexts with many
-(layer, head) cells.  Covered: 1 .. 5 streams per block, a last group of fewer streams, 8 keep levels (78 KB of LDS)."""
+(layer, head) cells.  Covered: 1 .. 5 streams per block, a last group of fewer streams, 8 keep levels (78 KB of LDS), and
+each arrangement of the attention launch's blocks."""
 import numpy as np
 import pytest
 import torch
@@ -21,6 +22,7 @@ CASES = [
     ("4 per block of 9: a last group of one", (29, 4, 64, 1, 20), ALL[:9], (20, 40)),
     ("5 per block of 6: a last group of one; 8 levels", (32, 8, 64, 2, 16), ALL[:6], LEVELS8),
     ("5 per block of 10; 8 levels and tokens nobody keeps", (16, 8, 70, 4, 8), ALL, LEVELS8),
+    ("one level; the matrix-core form's reference walks on", (16, 8, 64, 2, 16), ALL[:4], (30,)),
     ("two row blocks; hidden reference", (16, 8, 64, 7, 32), ALL[1:5], (32, 50, 63)),
 ]
 
