@@ -6,6 +6,7 @@ import subprocess
 
 import pytest
 
+import test_gpu_score_edges as edges
 import test_gpu_score_large as large
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -42,3 +43,8 @@ def test_shapes_of_the_large_call_tests_run_the_throughput_kernel(plan):
         assert _wide(plan, L, H, T, G, W), (L, H, T, G, W)
     for L, H, T, G, W, _, _ in large.SHAPES:
         assert not _wide(plan, L, H, T, G, W), (L, H, T, G, W)
+
+
+def test_shapes_of_the_edge_tests_run_both_kernels(plan):
+    assert [_wide(plan, *s) for s in edges.BOTH] == [True, True, False]
+    assert _wide(plan, 2, 8, 49152, 4, 32) and _wide(plan, 2, 8, 49152, 8, 64) and not _wide(plan, 1, 8, 4096, 4, 32)
