@@ -628,8 +628,8 @@ __global__ __launch_bounds__(kThreads, KVP_EVAL_WAVES_PER_SIMD) void attention_k
 // by the sum merged the same way; the reference goes through the same steps, so that the identity candidate differs from
 // it by exactly nothing.  A stored output is 256 runs of 64 floats (one run per thread of attention_kernel); here
 // consecutive threads read consecutive 16-byte pieces, and the query row a piece belongs to follows from its position.
-// Bound by the reads of the stored outputs: 40 levels of 256 cells in 126 us (5.9 TB/s of the 0.74 GB read; a block per
-// stream that merges the reference for itself: 280 us).
+// Bound by the reads of the stored outputs: 40 levels of 256 cells in 125 us (0.81 GB with the reference read by both
+// blocks of a cell, 0.75 GB of it from HBM: 6.0 TB/s; a block per stream that merges the reference for itself: 280 us).
 constexpr int kCompareThreads = 1024;
 constexpr int kMaxStreamsPerBlock = 5;
 struct MergeFactors { float keep, add, inv; };

@@ -25,8 +25,8 @@
 // What bounds it (throughput kernel): the issue of matrix and vector instructions together, at the 1.9-2.0 GHz the chip holds
 // under this load.  A product of 32x32x16 takes 32 cycles of the matrix pipe; the six vector instructions that go with
 // it (two logits, two exponentials of 8 cycles, two sums) take 32 cycles, and 42 together measured in isolation with two
-// waves per SIMD; 65 in the kernel.  Hence (80 x 8 x 16384 keys, 512 rows: 3.17 -> 2.73 ms; 28 x 4 x 131072, 224 rows:
-// 2.31 -> 1.93 ms):
+// waves per SIMD; 65 in the kernel.  Hence (80 x 8 x 16384 keys, 512 rows: 3.23 -> 2.76 ms; 28 x 4 x 131072, 224 rows:
+// 2.36 -> 1.97 ms):
 //   - 64 keys per wave: a query operand read from LDS serves two products;
 //   - the products of one tile are interleaved with the vector instructions of the tile before in program order, across
 //     query tiles and key units, so that both pipes have work whatever the other wave of the SIMD does;
