@@ -26,7 +26,7 @@ constexpr int kCUs = 256;                          // one block of 8 waves each
 // rows.  Faster inside a row, but a block goes through its parts of the rows one after the other, and each of them costs
 // staging, references and four barriers, and waits for its last wave; two or three blocks per CU measured 2 and 4 % slower.
 // So it needs rows of many units and many units per block, or a chunked kernel whose last round of blocks leaves much of the
-// chip idle.  Both were timed over 1850 shapes (rows of 1 .. 2048 units, calls of 512 .. 163840 units, M = 8 .. 512).  Time of
+// chip idle.  Both were timed over 2800 shapes (rows of 1 .. 2048 units, calls of 512 .. 163840 units, M = 8 .. 512).  Time of
 // the throughput kernel over the chunked one:
 //   rows of 4, 16, 32, 48, 64, 256 units, 160 units per block: M = 512 1.87, 1.27, 1.09, 0.92, 0.90, 0.80; M = 8 1.51, 1.09,
 //     0.94, 0.88, 0.86, 0.92.  The line lies at 48 and 32;
@@ -35,7 +35,8 @@ constexpr int kCUs = 256;                          // one block of 8 waves each
 //   otherwise, with 24 units per block, when the chunked kernel's rounds hold 1.2 times its work (1.6 for rows of 16 .. 31
 //     units; 1.1 and 12 units for rows of 1024): 0.68 for rows of 40 units of which a call has 3.2 rounds of blocks, 0.8 at
 //     118 units and 3.1 rounds, 0.78 at 1793 units and 3.5 rounds.
-// With these lines the kernel taken is 0.3 % slower than the better one on average, and by more than 5 % for 1 shape in 40.
+// With these lines the kernel taken is 0.6 % slower than the better one on average over 2600 shapes of at least 1500 units,
+// and by more than 5 % for 1 in 23 (with the line at 2048 units in the call alone: 13 %, and 2 in 5).
 struct ScorePlan {
   int32_t M, nqt, Mrows;
   int32_t chunk_keys;                              // keys per block (chunked kernel)
